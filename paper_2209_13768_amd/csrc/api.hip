@@ -70,7 +70,8 @@ Layout layout_for(int nx, int ny, int nz, int precision) {
   L.scalars = take(sizeof(Scalars) * 4);
   // one launch per pass: up to kMaxReduce values per tile slot (the
   // two-reduction BiCGStab's second pass reduces four); persistent launches
-  // keep the three phases' partials apart (3 x tiles + 2 x pointwise blocks)
+  // keep the three phases' partials apart (3 x tiles + 2 x pointwise blocks),
+  // resident iterations their exchange slots behind the per-pass partials
   L.partials = take(sizeof(double) * (kMaxReduce * partial_slots(nx, ny, nz) + 2 * 2048));
   if (precision == WFA_F32_IR64) {
     L.b64 = take(8 * n);
@@ -152,6 +153,7 @@ void grid_setup(wfa_grid* g, int nx, int ny, int nz, const wfa_coeffs* c, char* 
   g->sc_in = g->sc + 1;
   g->sc_aux = g->sc + 2;
   g->partials = (double*)(ws + g->lay.partials);
+  g->ring = g->partials + kMaxReduce * partial_slots(nx, ny, nz);
   for (int q = 0; q < kVecs; ++q) g->vec[q] = ws + g->lay.vec[q];
   g->b64 = g->prec == WFA_F32_IR64 ? (double*)(ws + g->lay.b64) : nullptr;
   g->d32 = g->prec == WFA_F32_IR64 ? (float*)(ws + g->lay.d32) : nullptr;
@@ -443,6 +445,7 @@ Launch<double> ctx<double>(wfa_grid* g, Scalars* sc, hipStream_t s) {
   L.cell = g->c.mode == WFA_COEF_CELL;
   L.kappa = (const float*)g->c.kappa;
   L.partials = g->partials;
+  L.ring = g->ring;
   L.sc = sc;
   L.stream = s;
   return L;
@@ -457,6 +460,7 @@ Launch<float> ctx<float>(wfa_grid* g, Scalars* sc, hipStream_t s) {
   L.cell = g->c.mode == WFA_COEF_CELL;
   L.kappa = (const float*)g->c.kappa;
   L.partials = g->partials;
+  L.ring = g->ring;
   L.sc = sc;
   L.stream = s;
   return L;
@@ -556,6 +560,14 @@ static int read_scalars(wfa_grid* g, const Scalars* dev, Scalars* host, hipStrea
 
 static int write_scalars(const Scalars* host, Scalars* dev, hipStream_t s) {
   launch_set_scalars(dev, *host, s);
+  return check_launch("set scalars");
+}
+
+// The scalars of a solve that may iterate resident.
+template <typename T>
+static int write_solve_scalars(const Launch<T>& L, const Scalars* host) {
+  if (L.tl.geo.ntiles > kResidentTiles) return write_scalars(host, L.sc, L.stream);
+  launch_set_resident(L.sc, *host, L.ring, L.tl.geo.ntiles, L.stream);
   return check_launch("set scalars");
 }
 
@@ -712,6 +724,28 @@ static void graph_key(uint64_t (&k)[GraphCache::kKey], const wfa_grid* g, const 
 }
 
 // ---------------------------------------------------------------------------
+// resident iterations
+// ---------------------------------------------------------------------------
+// Grids whose tiles all fit on the chip with their vectors in registers
+// iterate in one cooperative launch per chunk (resident.hip): bitwise the
+// iterates of one launch per pass.  Not where the caller asked for another
+// launch form or for per-launch timing, and not without a pinned block (the
+// allocation-free solve: a first cooperative launch makes the runtime create
+// a queue).
+template <typename T>
+static bool use_resident(const wfa_grid* g, const Launch<T>& L, int kind) {
+  if (g->profile || g->persistent != 0 || g->recompute_t || g->rb.sync || use_graph(g)) return false;
+  return resident_fits<T>(L, kind);
+}
+
+// Iterations of one resident launch: the solve leaves it when it ends, so
+// only the host's own checks bound it (WFA_OPT_CHECK_EVERY).
+static int resident_chunk(const wfa_grid* g, int budget) {
+  const int m = g->check_every > 0 ? g->check_every : 512;
+  return m < budget ? m : budget < 1 ? 1 : budget;
+}
+
+// ---------------------------------------------------------------------------
 // BiCGStab (and CG) iteration loops on an initialised scalar block
 // ---------------------------------------------------------------------------
 // Runs iterations until the device status leaves ST_RUN.  A breakdown
@@ -740,7 +774,10 @@ static int read_chunk(wfa_grid* g, const Scalars* dev, Scalars* h, hipStream_t s
     int rc = check_launch("tail");
     if (rc) return rc;
   }
-  return read_scalars(g, dev, h, s, tail ? tail->dev : nullptr, tail ? tail->host : nullptr);
+  const int rc = read_scalars(g, dev, h, s, tail ? tail->dev : nullptr, tail ? tail->host : nullptr);
+  if (rc) return rc;
+  if (h->timeout) return set_error(WFA_ERR_HIP, "resident iterations: an exchange timed out");
+  return WFA_OK;
 }
 
 template <typename T>
@@ -829,6 +866,7 @@ static int iterate_bicgstab2(wfa_grid* g, const Launch<T>& L, T* x, T** r, T* rh
   // With recompute_t pass 1 forms t = A s again and pass 2 stores nothing:
   // bitwise the same iterates, two vector streams fewer per iteration.
   const bool recompute = g->recompute_t != 0;
+  const bool resident = use_resident(g, L, kResidentBicgstab2);
   auto pass_pair = [&](const Launch<T>& Lp, int pp) {
     {
       ProfScope ps(g, WFA_K_PHASE_AC, Lp.stream);
@@ -852,6 +890,18 @@ static int iterate_bicgstab2(wfa_grid* g, const Launch<T>& L, T* x, T** r, T* rh
       }
       if ((rc = check_launch("init"))) return rc;
       h->restart = 0;
+      continue;
+    }
+    if (resident) {
+      const int m = resident_chunk(g, h->maxit - h->iter + 1);
+      T* const rb[2] = {r[0], r[1]};
+      T* const pb[2] = {p[0], p[1]};
+      T* const vb[2] = {v[0], v[1]};
+      const hipError_t e = launch_resident<T>(L, kResidentBicgstab2, x, rb, rh, pb, vb, t, m, par);
+      if (e != hipSuccess)
+        return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
+      par ^= m & 1;
+      if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
       continue;
     }
     // maxit iterations take maxit + 1 first passes (the last applies the update)
@@ -929,7 +979,20 @@ static int iterate_cg1(wfa_grid* g, const Launch<T>& L, T* x, T** r, T** w, T** 
                        Scalars* h, ChunkTail* tail, int hint) {
   int par = 0;
   int rc = WFA_OK;
+  const bool resident = use_resident(g, L, kResidentCg1);
   while (h->status == ST_RUN) {
+    if (resident) {
+      const int m = resident_chunk(g, h->maxit - h->iter + (h->stage == 0 ? 1 : 0));
+      T* const rb[2] = {r[0], r[1]};
+      T* const sb[2] = {sv[0], sv[1]};
+      T* const wb[2] = {w[0], w[1]};
+      const hipError_t e = launch_resident<T>(L, kResidentCg1, x, rb, nullptr, sb, wb, p, m, par);
+      if (e != hipSuccess)
+        return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
+      par ^= m & 1;
+      if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
+      continue;
+    }
     // passes still needed: the iterations left, and w0 = A r0 if not formed
     const int m = next_chunk(g, *h, h->maxit - h->iter + (h->stage == 0 ? 1 : 0), hint);
     int k = 0;
@@ -1001,9 +1064,9 @@ static int solve_plain(wfa_grid* g, const T* b_user, T* x, bool form_b, double t
   T* bw = vec[7];
   Scalars h = fresh_scalars(tol, maxit, g->force_bd);
   g->force_bd = 0;
-  int rc = write_scalars(&h, g->sc, s);
-  if (rc) return rc;
   Launch<T> L = ctx<T>(g, g->sc, s);
+  int rc = write_solve_scalars(L, &h);
+  if (rc) return rc;
   L.shadow = g->method == WFA_METHOD_BICGSTAB2 ? g->shadow : 0;
   const T* b = form_b ? bw : b_user;
   {
@@ -1140,7 +1203,7 @@ static int solve_ir(wfa_grid* g, const double* b_user, double* x, bool form_b, d
     hi.guard = inner_cap > 0 ? 0.0 : kIrGuard;
     hi.force_div = ref == 0 ? force_div : 0;
     if ((rc = write_scalars(&ho, g->sc, s))) return rc;
-    if ((rc = write_scalars(&hi, g->sc_in, s))) return rc;
+    if ((rc = write_solve_scalars(L32, &hi))) return rc;
     {
       ProfScope ps(g, WFA_K_RESIDUAL, s);
       launch_residual<double>(L64, x, b, r, rh, g->sc_in, cg1 ? 1 : 2, shadow);
