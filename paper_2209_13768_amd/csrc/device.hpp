@@ -315,9 +315,40 @@ __device__ __forceinline__ void dot_acc(double& a, double x, double y) {
   a = __builtin_fma(x, y, a);
 }
 
+// Sum over the wave, in every lane: the butterfly v += v of lane ^ m for m =
+// 32, 16, ..., 1 (a sum's two operands may change places, so each step's
+// bits are the same in both lanes).  The partners come through register
+// moves instead of shuffles through LDS, whose six dependent trips were a
+// good part of a small grid's pass: the half and quarter swaps, then
+// rotations of a 16-lane row by 8 and by 4 (after the step before, a row
+// repeats with that period, so the rotation brings lane ^ 8 and lane ^ 4's
+// value) and permutations inside four lanes.
+__device__ __forceinline__ double from_words(uint32_t lo, uint32_t hi) {
+  return __hiloint2double((int)hi, (int)lo);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+  {
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = from_words(l[0], h[0]) + from_words(l[1], h[1]);
+  }
+  {
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = from_words(l[0], h[0]) + from_words(l[1], h[1]);
+  }
+  v += dpp_move<0x128>(v);   // row_ror:8
+  v += dpp_move<0x124>(v);   // row_ror:4
+  v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
+  v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
   return v;
 }
 
