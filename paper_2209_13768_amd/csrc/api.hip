@@ -71,7 +71,7 @@ Layout layout_for(int nx, int ny, int nz, int precision) {
   // one launch per pass: up to kMaxReduce values per tile slot (the
   // two-reduction BiCGStab's second pass reduces four); persistent launches
   // keep the three phases' partials apart (3 x tiles + 2 x pointwise blocks),
-  // resident iterations their exchange slots behind the per-pass partials
+  // resident iterations their exchange slots behind the partials
   L.partials = take(sizeof(double) * (kMaxReduce * partial_slots(nx, ny, nz) + 2 * 2048));
   if (precision == WFA_F32_IR64) {
     L.b64 = take(8 * n);
@@ -153,7 +153,6 @@ void grid_setup(wfa_grid* g, int nx, int ny, int nz, const wfa_coeffs* c, char* 
   g->sc_in = g->sc + 1;
   g->sc_aux = g->sc + 2;
   g->partials = (double*)(ws + g->lay.partials);
-  g->ring = g->partials + kMaxReduce * partial_slots(nx, ny, nz);
   for (int q = 0; q < kVecs; ++q) g->vec[q] = ws + g->lay.vec[q];
   g->b64 = g->prec == WFA_F32_IR64 ? (double*)(ws + g->lay.b64) : nullptr;
   g->d32 = g->prec == WFA_F32_IR64 ? (float*)(ws + g->lay.d32) : nullptr;
@@ -436,6 +435,17 @@ extern "C" int wfa_kernel_stats(wfa_grid* g, int kernel, int64_t* launches, doub
 template <typename T>
 static Launch<T> ctx(wfa_grid* g, Scalars* sc, hipStream_t s);
 
+// The exchange slots of resident iterations lie behind the partial sums of
+// the per-pass launches a resident solve still makes (initial and true
+// residual: kMaxReduce per tile), in the rest of the partials' space.
+template <typename T>
+static void set_ring(const wfa_grid* g, Launch<T>& L) {
+  const size_t used = (size_t)kMaxReduce * L.tl.geo.ntiles;
+  const size_t all = kMaxReduce * partial_slots(g->nx, g->ny, g->nz) + 2 * 2048;
+  L.ring = g->partials + used;
+  L.ring_copies = ring_copies(all - used, L.tl.geo.ntiles);
+}
+
 template <>
 Launch<double> ctx<double>(wfa_grid* g, Scalars* sc, hipStream_t s) {
   Launch<double> L{};
@@ -445,7 +455,7 @@ Launch<double> ctx<double>(wfa_grid* g, Scalars* sc, hipStream_t s) {
   L.cell = g->c.mode == WFA_COEF_CELL;
   L.kappa = (const float*)g->c.kappa;
   L.partials = g->partials;
-  L.ring = g->ring;
+  set_ring(g, L);
   L.sc = sc;
   L.stream = s;
   return L;
@@ -460,7 +470,7 @@ Launch<float> ctx<float>(wfa_grid* g, Scalars* sc, hipStream_t s) {
   L.cell = g->c.mode == WFA_COEF_CELL;
   L.kappa = (const float*)g->c.kappa;
   L.partials = g->partials;
-  L.ring = g->ring;
+  set_ring(g, L);
   L.sc = sc;
   L.stream = s;
   return L;
@@ -567,7 +577,7 @@ static int write_scalars(const Scalars* host, Scalars* dev, hipStream_t s) {
 template <typename T>
 static int write_solve_scalars(const Launch<T>& L, const Scalars* host) {
   if (L.tl.geo.ntiles > kResidentTiles) return write_scalars(host, L.sc, L.stream);
-  launch_set_resident(L.sc, *host, L.ring, L.tl.geo.ntiles, L.stream);
+  launch_set_resident(L.sc, *host, L.ring, L.ring_copies, L.tl.geo.ntiles, L.stream);
   return check_launch("set scalars");
 }
 

@@ -96,7 +96,6 @@ struct wfa_grid {
   wfa::Scalars* sc_in;   // inner solve of iterative refinement
   wfa::Scalars* sc_aux;  // true residual
   double* partials;
-  double* ring;          // exchange slots of the resident iterations (behind the partials)
   void* vec[wfa::kVecs];
   double* b64;
   float* d32;

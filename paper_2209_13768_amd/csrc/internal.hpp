@@ -31,6 +31,7 @@ struct Launch {
   Scalars* sc;
   hipStream_t stream;
   double* ring;   // exchange slots of the resident iterations
+  int ring_copies;
   int shadow;   // 1: the two-reduction BiCGStab's shadow residual is index-hashed
 };
 
@@ -121,14 +122,16 @@ hipError_t launch_persistent_bicgstab(const Launch<T>& L, T* x, T* r, const T* r
 // vectors in registers; the iterates bitwise those of the per-pass
 // launches).  r, p, v: the double-buffered pairs, those of `parity` in.
 enum ResidentKind { kResidentBicgstab2 = 0, kResidentCg1 = 1 };
-constexpr int kResidentTiles = 256;   // most tiles: the ring holds 12 doubles a tile
+constexpr int kResidentTiles = 256;   // most tiles (one workgroup per CU)
+int ring_copies(size_t doubles, int ntiles);
 template <typename T>
 bool resident_fits(const Launch<T>& L, int kind);
 template <typename T>
 hipError_t launch_resident(const Launch<T>& L, int kind, T* x, T* const (&r)[2], const T* rh,
                            T* const (&p)[2], T* const (&v)[2], T* t, int iters, int parity);
 // launch_set_scalars, and the ring of a grid of `ntiles` tiles emptied
-void launch_set_resident(Scalars* dst, const Scalars& v, double* ring, int ntiles, hipStream_t s);
+void launch_set_resident(Scalars* dst, const Scalars& v, double* ring, int copies, int ntiles,
+                         hipStream_t s);
 
 // Streams a probe kind reads and writes: `bytes` each (a copy: 2; a stream
 // mix: its reads and writes).

@@ -35,8 +35,8 @@
 // finalizer runs on registers.
 //
 // Measured (us an iteration, one launch per pass -> resident):
-//   two-reduction BiCGStab, FP64   32^3 19.9 -> 6.6    64^3 26.0 -> 10.6
-//   CG, one reduction, FP64        32^3 10.5 -> 3.3    64^3 14.2 -> 4.8
+//   two-reduction BiCGStab, FP64   32^3 20.0 -> 5.8    64^3 25.8 -> 9.4
+//   CG, one reduction, FP64        32^3 10.5 -> 3.0    64^3 14.4 -> 4.4
 //   (8.9 / 15.1 and 4.6 / 7.1 where a pass waited for its stores before it
 //   published its sums, with branches around the cells outside the grid)
 //
@@ -81,7 +81,8 @@ struct ResArgs {
   T* t;
   T *r[2], *p[2], *v[2];
   T* set[kRing];     // exchange vectors; set[0] is not read when the launch starts
-  double* ring;      // kRing sets of kMaxReduce x ntiles slots
+  double* ring;      // `copies` rings of kRing sets of kMaxReduce x ntiles slots
+  int copies;
   Scalars* sc;
   int iters;
   int parity;
@@ -407,19 +408,36 @@ __device__ __forceinline__ double sum_waves(const double* red, int q) {
   return s;
 }
 
+// The slots of the partial sums.  Every workgroup reads all of them, and
+// hundreds of readers of one line queue up at its home; a tile therefore
+// writes its sums to several copies of the ring, and workgroups that fall to
+// different XCDs read different ones.
+struct Ring {
+  Rsrc slots;
+  int copies, nt, read;   // read: first slot of the copy this workgroup reads
+  __device__ Ring(double* p, int copies_, int nt_)
+      : slots(rsrc(p, (size_t)copies_ * kRing * kMaxReduce * nt_ * 8)), copies(copies_), nt(nt_),
+        read(((int)blockIdx.x % copies_) * kRing * kMaxReduce * nt_) {}
+};
+
 // Exchange number `seq` of the solve: publishes this tile's sums, waits for
 // every tile's sums and this tile's halo cells (`poll` loads them and says
 // whether one is empty), and leaves the grid's sums in v, in thread 0 (the
 // order of publish_and_finalize).  False once a wait has given up.
 template <int NV, class Poll>
-__device__ __forceinline__ bool exchange(double (&v)[NV], Rsrc ring, int tile, int nt, int seq,
+__device__ __forceinline__ bool exchange(double (&v)[NV], const Ring& ring, int tile, int seq,
                                          double (&red)[2][kWaves * kMaxReduce], int* bad,
                                          Poll poll) {
-  const int set = (seq % kRing) * kMaxReduce * nt, was = ((seq + kRing - 1) % kRing) * kMaxReduce * nt;
+  const int nt = ring.nt;
+  const int set = (seq % kRing) * kMaxReduce * nt;
+  const int was = ((seq + kRing - 1) % kRing) * kMaxReduce * nt;
   const int t = threadIdx.x;
+  const int tq = t % kMaxReduce, tc = t / kMaxReduce;   // slot and copy of a storing thread
+  const int mine = (tc * kRing * kMaxReduce + tq) * nt + tile;
   wave_sums<NV>(v, red[0]);
   __syncthreads();
-  if (t < NV) put_value(ring, (set + t * nt + tile) * 8, sum_waves<NV>(red[0], t));
+  if (tq < NV && tc < ring.copies)
+    put_value(ring.slots, (set + mine) * 8, sum_waves<NV>(red[0], tq));
   double got[NV];
   bool wait;
   int spins = 0;
@@ -427,7 +445,8 @@ __device__ __forceinline__ bool exchange(double (&v)[NV], Rsrc ring, int tile, i
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int q = 0; q < NV; ++q)
-      got[q] = buf_load<double, kAgent>(ring, t < nt ? (set + q * nt + t) * 8 : kNowhere);
+      got[q] = buf_load<double, kAgent>(
+          ring.slots, t < nt ? (ring.read + set + q * nt + t) * 8 : kNowhere);
     wait = poll();
 #pragma unroll
     for (int q = 0; q < NV; ++q) wait = wait | is_empty(got[q]);
@@ -441,7 +460,7 @@ __device__ __forceinline__ bool exchange(double (&v)[NV], Rsrc ring, int tile, i
 #pragma unroll
   for (int q = 0; q < NV; ++q) v[q] = sum_waves<NV>(red[1], q);
   // every workgroup has read the slots before: empty this tile's
-  if (t < kMaxReduce) put_empty<double>(ring, (was + t * nt + tile) * 8);
+  if (tc < ring.copies) put_empty<double>(ring.slots, (was + mine) * 8);
   return *bad == 0;
 }
 
@@ -459,13 +478,13 @@ __device__ __forceinline__ void finalize(Scalars& sc, const double (&v)[NV]) {
 // cells, the exchange vectors' boundary cells are emptied (the first vector,
 // which nobody loads, before).  One exchange without values.
 template <typename T, class Tile>
-__device__ __forceinline__ bool open_sets(const ResArgs<T>& a, const Tile& tl, Rsrc ring, int tile,
-                                          int& seq, double (&red)[2][kWaves * kMaxReduce],
-                                          int* bad) {
+__device__ __forceinline__ bool open_sets(const ResArgs<T>& a, const Tile& tl, const Ring& ring,
+                                          int tile, int& seq,
+                                          double (&red)[2][kWaves * kMaxReduce], int* bad) {
   tl.empty_boundary(a.set[0]);
   stores_done();
   double none[1] = {0.0};
-  if (!exchange<1>(none, ring, tile, a.geo.ntiles, seq++, red, bad, [] { return false; }))
+  if (!exchange<1>(none, ring, tile, seq++, red, bad, [] { return false; }))
     return false;
   tl.empty_boundary(a.set[1]);
   tl.empty_boundary(a.set[2]);
@@ -513,7 +532,6 @@ __global__ void __launch_bounds__(kThreads) k_resident_bicgstab2(ResArgs<T> a) {
   using Tile = ResTile<T, CELL, Z>;
   __shared__ ResShared<T, CELL, Z> sh;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int nt = a.geo.ntiles;
   if (threadIdx.x == 0) {
     sh.sc = *a.sc;
     sh.bad = 0;
@@ -521,7 +539,7 @@ __global__ void __launch_bounds__(kThreads) k_resident_bicgstab2(ResArgs<T> a) {
   __syncthreads();
   if (sh.sc.status != ST_RUN || sh.sc.restart) return;
   Tile tl(a.geo, a.op, sh, tile, a.kappa);
-  const Rsrc ring = rsrc(a.ring, (size_t)kRing * kMaxReduce * nt * 8);
+  const Ring ring(a.ring, a.copies, a.geo.ntiles);
   int par = a.parity;
   int seq = sh.sc.seq;
   typename Tile::Own r, p, v, t, x, rh, u;
@@ -593,7 +611,7 @@ __global__ void __launch_bounds__(kThreads) k_resident_bicgstab2(ResArgs<T> a) {
       dot_acc(s3[1], (double)rh[k][q], (double)r[k][q]);
       dot_acc(s3[2], (double)r[k][q], (double)r[k][q]);
     }
-    ok = exchange<3>(s3, ring, tile, nt, seq++, sh.red, &sh.bad, [&] {
+    ok = exchange<3>(s3, ring, tile, seq++, sh.red, &sh.bad, [&] {
       tl.template load_halo<kAgent>(sets.cur, hv, zv);
       return tl.halo_empty(hv, zv);
     });
@@ -624,7 +642,7 @@ __global__ void __launch_bounds__(kThreads) k_resident_bicgstab2(ResArgs<T> a) {
       dot_acc(s4[2], (double)rh[k][q], (double)u[k][q]);
       dot_acc(s4[3], (double)rh[k][q], (double)t[k][q]);
     }
-    ok = exchange<4>(s4, ring, tile, nt, seq++, sh.red, &sh.bad, [&] {
+    ok = exchange<4>(s4, ring, tile, seq++, sh.red, &sh.bad, [&] {
       tl.template load_halo<kAgent>(sets.cur, ht, zt);
       return tl.halo_empty(ht, zt);
     });
@@ -652,7 +670,6 @@ __global__ void __launch_bounds__(kThreads) k_resident_cg1(ResArgs<T> a) {
   using Tile = ResTile<T, CELL, Z>;
   __shared__ ResShared<T, CELL, Z> sh;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int nt = a.geo.ntiles;
   if (threadIdx.x == 0) {
     sh.sc = *a.sc;
     sh.bad = 0;
@@ -660,7 +677,7 @@ __global__ void __launch_bounds__(kThreads) k_resident_cg1(ResArgs<T> a) {
   __syncthreads();
   if (sh.sc.status != ST_RUN || sh.sc.restart) return;
   Tile tl(a.geo, a.op, sh, tile, a.kappa);
-  const Rsrc ring = rsrc(a.ring, (size_t)kRing * kMaxReduce * nt * 8);
+  const Ring ring(a.ring, a.copies, a.geo.ntiles);
   int par = a.parity;
   int seq = sh.sc.seq;
   typename Tile::Own r, w, s, p, x;
@@ -724,7 +741,7 @@ __global__ void __launch_bounds__(kThreads) k_resident_cg1(ResArgs<T> a) {
       dot_acc(s2[0], (double)r[k][q], (double)r[k][q]);
       dot_acc(s2[1], (double)w[k][q], (double)r[k][q]);
     }
-    ok = exchange<2>(s2, ring, tile, nt, seq++, sh.red, &sh.bad, [&] {
+    ok = exchange<2>(s2, ring, tile, seq++, sh.red, &sh.bad, [&] {
       tl.template load_halo<kAgent>(sets.cur, hw, zw);
       return tl.halo_empty(hw, zw);
     });
@@ -810,6 +827,7 @@ hipError_t launch_resident(const Launch<T>& L, int kind, T* x, T* const (&r)[2],
     a.set[0] = r[parity ^ 1]; a.set[1] = t; a.set[2] = r[parity];
   }
   a.ring = L.ring;
+  a.copies = L.ring_copies;
   a.sc = L.sc;
   a.iters = iters;
   a.parity = parity;
@@ -820,15 +838,23 @@ hipError_t launch_resident(const Launch<T>& L, int kind, T* x, T* const (&r)[2],
 }
 
 // The solve's scalars, with every slot of the ring empty.
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(1024)
 k_set_resident(Scalars* __restrict__ dst, Scalars v, uint64_t* __restrict__ ring, int slots) {
   if (threadIdx.x == 0) *dst = v;
-  for (int e = threadIdx.x; e < slots; e += kThreads) ring[e] = Empty<double>::value;
+  for (int e = threadIdx.x; e < slots; e += 1024) ring[e] = Empty<double>::value;
 }
 
-void launch_set_resident(Scalars* dst, const Scalars& v, double* ring, int ntiles, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_resident, dim3(1), dim3(kThreads), 0, s, dst, v, (uint64_t*)ring,
-                     kRing * kMaxReduce * ntiles);
+void launch_set_resident(Scalars* dst, const Scalars& v, double* ring, int copies, int ntiles,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(k_set_resident, dim3(1), dim3(1024), 0, s, dst, v, (uint64_t*)ring,
+                     copies * kRing * kMaxReduce * ntiles);
+}
+
+// Copies of the ring that fit in `doubles` (a power of two, one per XCD at most).
+int ring_copies(size_t doubles, int ntiles) {
+  int c = 8;
+  while (c > 1 && (size_t)c * kRing * kMaxReduce * ntiles > doubles) c /= 2;
+  return c;
 }
 
 #define WFA_RES(T)                                                                             \
