@@ -16,7 +16,13 @@ struct Tiling {
   int ry;          // rows per wave (TY = 4 * ry)
   Geo geo;         // tile grid
   int pw_blocks;   // workgroups of the pointwise kernels
+  bool tile_order; // the pointwise kernels sum in the tiles' order instead
 };
+// Tilings whose tiles may stay on the chip for a chunk of iterations, in
+// registers: at most one tile per CU, of two rows per wave and few planes.
+constexpr int kTileOrderRows = 2;
+constexpr int kResidentTiles = 256;
+constexpr int kResidentPlanes = 4;
 
 Tiling make_tiling(int nx, int ny, int nz, int elem_bytes, int zc_override, int ry_override);
 
@@ -122,7 +128,6 @@ hipError_t launch_persistent_bicgstab(const Launch<T>& L, T* x, T* r, const T* r
 // vectors in registers; the iterates bitwise those of the per-pass
 // launches).  r, p, v: the double-buffered pairs, those of `parity` in.
 enum ResidentKind { kResidentBicgstab2 = 0, kResidentCg1 = 1 };
-constexpr int kResidentTiles = 256;   // most tiles (one workgroup per CU)
 int ring_copies(size_t doubles, int ntiles);
 template <typename T>
 bool resident_fits(const Launch<T>& L, int kind);

@@ -256,26 +256,34 @@ void launch_set_scalars(Scalars* dst, const Scalars& v, hipStream_t s) {
 // ============================================================================
 // pointwise kernels
 // ============================================================================
-template <typename T>
+// TILES: in the order of the stencil passes' tiles (Tiling::tile_order).
+template <typename T, bool TILES>
 __global__ void __launch_bounds__(kThreads)
-k_phase_c(size_t n, T* __restrict__ x, const T* __restrict__ p, T* __restrict__ r,
+k_phase_c(Geo g, T* __restrict__ x, const T* __restrict__ p, T* __restrict__ r,
           const T* __restrict__ v, const T* __restrict__ t, const T* __restrict__ rh,
           double* partials, Scalars* sc) {
   __shared__ double red[kWaves * 2];
   if (sc->status != ST_RUN || sc->restart) return;
   double acc[2] = {0.0, 0.0};
-  phase_c_range<T>(n, blockIdx.x, gridDim.x, x, p, r, v, t, rh, sc, acc);
+  if constexpr (TILES)
+    phase_c_tile<T, kTileOrderRows>(g, blockIdx.x, x, p, r, v, t, rh, sc, acc);
+  else
+    phase_c_range<T>((size_t)g.plane * (size_t)g.nz, blockIdx.x, gridDim.x, x, p, r, v, t, rh, sc,
+                     acc);
   publish_and_finalize<2>(acc, blockIdx.x, gridDim.x, partials, sc, red, FinC{sc});
 }
 
-template <typename T>
+template <typename T, bool TILES>
 __global__ void __launch_bounds__(kThreads)
-k_cg_b(size_t n, T* __restrict__ x, const T* __restrict__ d, T* __restrict__ r,
+k_cg_b(Geo g, T* __restrict__ x, const T* __restrict__ d, T* __restrict__ r,
        const T* __restrict__ q, double* partials, Scalars* sc) {
   __shared__ double red[kWaves];
   if (sc->status != ST_RUN) return;
   double acc[1] = {0.0};
-  cg_b_range<T>(n, blockIdx.x, gridDim.x, x, d, r, q, sc, acc);
+  if constexpr (TILES)
+    cg_b_tile<T, kTileOrderRows>(g, blockIdx.x, x, d, r, q, sc, acc);
+  else
+    cg_b_range<T>((size_t)g.plane * (size_t)g.nz, blockIdx.x, gridDim.x, x, d, r, q, sc, acc);
   publish_and_finalize<1>(acc, blockIdx.x, gridDim.x, partials, sc, red, FinCgB{sc});
 }
 
@@ -294,19 +302,27 @@ __global__ void __launch_bounds__(kThreads) k_fill(size_t n, T* __restrict__ y, 
   for (size_t e = (size_t)blockIdx.x * kThreads + threadIdx.x; e < n; e += stride) y[e] = v;
 }
 
-static size_t cells_of(const Geo& g) { return (size_t)g.plane * (size_t)g.nz; }
-
 template <typename T>
 void launch_phase_c(const Launch<T>& L, T* x, const T* p, T* r, const T* v, const T* t,
                     const T* rh) {
-  hipLaunchKernelGGL(k_phase_c<T>, dim3(L.tl.pw_blocks), dim3(kThreads), 0, L.stream,
-                     cells_of(L.tl.geo), x, p, r, v, t, rh, L.partials, L.sc);
+  const Geo& g = L.tl.geo;
+  if (L.tl.tile_order)
+    hipLaunchKernelGGL((k_phase_c<T, true>), dim3(g.ntiles), dim3(kThreads), 0, L.stream, g, x, p, r,
+                       v, t, rh, L.partials, L.sc);
+  else
+    hipLaunchKernelGGL((k_phase_c<T, false>), dim3(L.tl.pw_blocks), dim3(kThreads), 0, L.stream, g,
+                       x, p, r, v, t, rh, L.partials, L.sc);
 }
 
 template <typename T>
 void launch_cg_b(const Launch<T>& L, T* x, const T* d, T* r, const T* q) {
-  hipLaunchKernelGGL(k_cg_b<T>, dim3(L.tl.pw_blocks), dim3(kThreads), 0, L.stream,
-                     cells_of(L.tl.geo), x, d, r, q, L.partials, L.sc);
+  const Geo& g = L.tl.geo;
+  if (L.tl.tile_order)
+    hipLaunchKernelGGL((k_cg_b<T, true>), dim3(g.ntiles), dim3(kThreads), 0, L.stream, g, x, d, r, q,
+                       L.partials, L.sc);
+  else
+    hipLaunchKernelGGL((k_cg_b<T, false>), dim3(L.tl.pw_blocks), dim3(kThreads), 0, L.stream, g, x,
+                       d, r, q, L.partials, L.sc);
 }
 
 void launch_promote(size_t n, int blocks, double* x, const float* d, const Scalars* sc_inner,
@@ -359,6 +375,16 @@ Tiling make_tiling(int nx, int ny, int nz, int elem_bytes, int zc_override, int 
   if (pb > 2048) pb = 2048;
   if (pb < 1) pb = 1;
   t.pw_blocks = (int)pb;
+  // The tile form of the pointwise passes.  Grids that may iterate resident
+  // need it: there a thread holds its tile's cells and forms their sums in
+  // that order.  Grids of four tiles a CU or more gain from its streaming
+  // hints and whole rows (textbook BiCGStab per iteration: 256^3 FP64 497 ->
+  // 441 us, 512^3 FP32 2350 -> 2264 us); between them a tile per workgroup
+  // is too few (161x97x113, 312 tiles: 107 -> 116 us).  zc >= 2: so many
+  // tiles' sums fit a persistent launch's regions.
+  t.tile_order = t.ry == kTileOrderRows &&
+                 ((g.ntiles <= kResidentTiles && g.zc <= kResidentPlanes) ||
+                  (g.ntiles >= 1024 && g.zc >= 2));
   (void)elem_bytes;
   return t;
 }

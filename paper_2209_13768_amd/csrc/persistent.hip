@@ -23,11 +23,12 @@ struct PersistArgs {
   Op<T> op;
   const float* kappa;
   T *x, *r, *rh, *t, *p0, *p1, *v0, *v1;
-  double* partials;  // regions: A [ntiles], B [2 ntiles], C [2 pw_blocks]
+  double* partials;  // regions: A [ntiles], B [2 ntiles], C [2 pw_blocks, or ntiles]
   Scalars* sc;
   GridBarrier* bar;
   size_t n;
   int pw_blocks;
+  int tile_order;
   int iters;
   int parity;
   int spin_limit;
@@ -43,7 +44,7 @@ __global__ void __launch_bounds__(kThreads) k_persistent_bicgstab(PersistArgs<T>
   if (threadIdx.x == 0) ls = *a.sc;
   __syncthreads();
   const Geo g = a.geo;
-  const int nt = g.ntiles, pw = a.pw_blocks;
+  const int nt = g.ntiles, pw = a.tile_order ? nt : a.pw_blocks;
   double* partA = a.partials;
   double* partB = a.partials + nt;
   double* partC = a.partials + 3 * (size_t)nt;
@@ -96,7 +97,10 @@ __global__ void __launch_bounds__(kThreads) k_persistent_bicgstab(PersistArgs<T>
     {
       for (int blk = blockIdx.x; blk < pw; blk += nb) {
         double acc[2] = {0.0, 0.0};
-        phase_c_range<T>(a.n, blk, pw, a.x, p_out, a.r, v_out, a.t, a.rh, &ls, acc);
+        if (a.tile_order)
+          phase_c_tile<T, RY>(g, blk, a.x, p_out, a.r, v_out, a.t, a.rh, &ls, acc);
+        else
+          phase_c_range<T>(a.n, blk, pw, a.x, p_out, a.r, v_out, a.t, a.rh, &ls, acc);
         block_sum<2>(acc, red);
         store_partial<2>(partC, pw, blk, acc);
       }
@@ -149,6 +153,7 @@ hipError_t launch_persistent_bicgstab(const Launch<T>& L, T* x, T* r, const T* r
   a.bar = bar;
   a.n = (size_t)L.tl.geo.plane * L.tl.geo.nz;
   a.pw_blocks = L.tl.pw_blocks;
+  a.tile_order = L.tl.tile_order;
   a.iters = iters;
   a.parity = parity;
   a.spin_limit = 1 << 22;

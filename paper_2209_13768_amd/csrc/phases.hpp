@@ -792,6 +792,46 @@ __device__ __forceinline__ bool aligned16(const void* a, const void* b, const vo
            ((uintptr_t)f)) & 15) == 0;
 }
 
+// The tile form (Tiling::tile_order): a workgroup covers the tile of the same
+// index and a thread the cells the stencil passes give it, planes in order
+// and then its rows.  use(index, ld(index)) for these cells, the loads of
+// kBatch planes in flight before the first is used.
+template <int RY, class Ld, class Use>
+__device__ __forceinline__ void tile_cells(const Geo& g, int tile, Ld ld, Use use) {
+  constexpr int kBatch = 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tx = tile % g.tiles_x;
+  const int rest = tile / g.tiles_x;
+  const int ty = rest % g.tiles_y;
+  const int tz = rest / g.tiles_y;
+  const int i = tx * kTX + lane, j0 = (ty * kWaves + wave) * RY;
+  const int k0 = tz * g.zc, k1 = min(k0 + g.zc, g.nz);
+  if (i >= g.nx) return;
+  const int rows = min(RY, g.ny - j0);
+  auto at = [&](int k, int r) {
+    return (size_t)k * (size_t)g.plane + (size_t)(j0 + r) * g.nx + i;
+  };
+  int k = k0;
+  if (rows == RY) {
+    for (; k + kBatch <= k1; k += kBatch) {
+      decltype(ld(size_t(0))) q[kBatch][RY];
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+        for (int r = 0; r < RY; ++r) q[b][r] = ld(at(k + b, r));
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+        for (int r = 0; r < RY; ++r) use(at(k + b, r), q[b][r]);
+    }
+  }
+  for (; k < k1; ++k)
+    for (int r = 0; r < rows; ++r) {
+      auto q = ld(at(k, r));
+      use(at(k, r), q);
+    }
+}
+
 template <typename T>
 __device__ __forceinline__ void phase_c_elem(T& x, T p, T& r, T v, T t, T rh, T alpha, T omega,
                                              bool xz, double (&acc)[2]) {
@@ -840,6 +880,13 @@ __device__ __forceinline__ void phase_c_range(size_t n, int blk, int blocks, T* 
 }
 
 template <typename T>
+__device__ __forceinline__ void cg_b_elem(T& x, T d, T& r, T q, T alpha, double (&acc)[1]) {
+  x = fma_t(alpha, d, x);
+  r = minus_ax(r, alpha, q);
+  dot_acc(acc[0], (double)r, (double)r);
+}
+
+template <typename T>
 __device__ __forceinline__ void cg_b_range(size_t n, int blk, int blocks, T* __restrict__ x,
                                            const T* __restrict__ d, T* __restrict__ r,
                                            const T* __restrict__ q, const Scalars* sc,
@@ -857,22 +904,55 @@ __device__ __forceinline__ void cg_b_range(size_t n, int blk, int blocks, T* __r
       VT xa = xv[e], ra = rv[e];
       const VT da = ((const VT*)d)[e], qa = ((const VT*)q)[e];
 #pragma unroll
-      for (int c = 0; c < N; ++c) {
-        xa.v[c] = fma_t(alpha, da.v[c], xa.v[c]);
-        ra.v[c] = minus_ax(ra.v[c], alpha, qa.v[c]);
-        dot_acc(acc[0], (double)ra.v[c], (double)ra.v[c]);
-      }
+      for (int c = 0; c < N; ++c) cg_b_elem<T>(xa.v[c], da.v[c], ra.v[c], qa.v[c], alpha, acc);
       xv[e] = xa;
       rv[e] = ra;
     }
     done = nv * N;
   }
-  for (size_t e = done + (size_t)blk * kThreads + threadIdx.x; e < n; e += stride) {
-    x[e] = fma_t(alpha, d[e], x[e]);
-    const T rn = minus_ax(r[e], alpha, q[e]);
-    r[e] = rn;
-    dot_acc(acc[0], (double)rn, (double)rn);
-  }
+  for (size_t e = done + (size_t)blk * kThreads + threadIdx.x; e < n; e += stride)
+    cg_b_elem<T>(x[e], d[e], r[e], q[e], alpha, acc);
+}
+
+template <typename T, int RY>
+__device__ __forceinline__ void phase_c_tile(const Geo& g, int tile, T* __restrict__ x,
+                                             const T* __restrict__ p, T* __restrict__ r,
+                                             const T* __restrict__ v, const T* __restrict__ t,
+                                             const T* __restrict__ rh, const Scalars* sc,
+                                             double (&acc)[2]) {
+  const T alpha = (T)sc->alpha, omega = (T)sc->omega;
+  const bool xz = sc->x_zero != 0;
+  struct Cell { T x, r, p, v, t, rh; };
+  tile_cells<RY>(
+      g, tile,
+      [&](size_t e) -> Cell {
+        return {xz ? T(0) : ld_once(x + e), ld_once(r + e), ld_once(p + e),
+                ld_once(v + e), ld_once(t + e), ld_once(rh + e)};
+      },
+      [&](size_t e, Cell& c) {
+        phase_c_elem<T>(c.x, c.p, c.r, c.v, c.t, c.rh, alpha, omega, xz, acc);
+        st_once(x + e, c.x);
+        st_once(r + e, c.r);
+      });
+}
+
+template <typename T, int RY>
+__device__ __forceinline__ void cg_b_tile(const Geo& g, int tile, T* __restrict__ x,
+                                          const T* __restrict__ d, T* __restrict__ r,
+                                          const T* __restrict__ q, const Scalars* sc,
+                                          double (&acc)[1]) {
+  const T alpha = (T)sc->alpha;
+  struct Cell { T x, r, d, q; };
+  tile_cells<RY>(
+      g, tile,
+      [&](size_t e) -> Cell {
+        return {ld_once(x + e), ld_once(r + e), ld_once(d + e), ld_once(q + e)};
+      },
+      [&](size_t e, Cell& c) {
+        cg_b_elem<T>(c.x, c.d, c.r, c.q, alpha, acc);
+        st_once(x + e, c.x);
+        st_once(r + e, c.r);
+      });
 }
 
 }  // namespace wfa

@@ -808,7 +808,7 @@ Entry<T> entry_for(const Launch<T>& L, int kind) {
 template <typename T>
 bool resident_fits(const Launch<T>& L, int kind) {
   const Geo& g = L.tl.geo;
-  if (L.tl.ry != 2 || g.ntiles > kResidentTiles) return false;
+  if (!L.tl.tile_order || g.ntiles > kResidentTiles) return false;
   return entry_for<T>(L, kind).fit >= g.ntiles;
 }
 
