@@ -241,13 +241,12 @@ enum {
   WFA_OPT_METHOD = 1,          /* WFA_METHOD_BICGSTAB (default), _CG,
                                   _BICGSTAB2 or _CG1 (used by wfa_timestep;
                                   the *_solve entry points name their method) */
-  WFA_OPT_PERSISTENT = 2,      /* 0 (default): one launch per phase, or, for
-                                  the two-reduction BiCGStab and the
-                                  one-reduction CG on grids small enough to
-                                  keep their vectors in registers, one
-                                  cooperative launch per chunk of iterations
-                                  (bitwise the same results; not with
-                                  WFA_OPT_PROFILE, _GRAPH or _RECOMPUTE_T),
+  WFA_OPT_PERSISTENT = 2,      /* 0 (default): one launch per phase, or, on
+                                  grids small enough to keep their vectors in
+                                  registers, one cooperative launch per chunk
+                                  of iterations (bitwise the same results; not
+                                  with WFA_OPT_PROFILE, _GRAPH or
+                                  _RECOMPUTE_T),
                                   1: one persistent launch per solve chunk,
                                   -1: automatic by grid size                   */
   WFA_OPT_PROFILE = 3,         /* n > 0: time every n-th launch of each

@@ -791,11 +791,12 @@ static int read_chunk(wfa_grid* g, const Scalars* dev, Scalars* h, hipStream_t s
 }
 
 template <typename T>
-static int iterate_bicgstab(wfa_grid* g, const Launch<T>& L, T* x, T* r, T* rh, T** p, T** v,
-                            T* t, const T* b, Scalars* h, int* restarts, bool restartable,
+static int iterate_bicgstab(wfa_grid* g, const Launch<T>& L, T* x, T* r, T* spare, T* rh, T** p,
+                            T** v, T* t, const T* b, Scalars* h, int* restarts, bool restartable,
                             ChunkTail* tail, int hint) {
   int par = 0;
   int rc = WFA_OK;
+  const bool resident = use_resident(g, L, kResidentBicgstab);
   if (use_persistent(g, L.tl)) {
     if ((rc = reset_barrier(g, L.stream))) return rc;
     if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
@@ -811,6 +812,16 @@ static int iterate_bicgstab(wfa_grid* g, const Launch<T>& L, T* x, T* r, T* rh, 
       if ((rc = check_launch("init"))) return rc;
       h->restart = 0;
       if (use_persistent(g, L.tl) && (rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
+      continue;
+    }
+    if (resident) {
+      const int m = resident_chunk(g, h->maxit - h->iter);
+      const ResidentVectors<T> vec{x, rh, t, {r, spare}, {p[0], p[1]}, {v[0], v[1]}};
+      const hipError_t e = launch_resident<T>(L, kResidentBicgstab, vec, m, par);
+      if (e != hipSuccess)
+        return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
+      par ^= m & 1;
+      if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
       continue;
     }
     const int m = next_chunk(g, *h, h->maxit - h->iter, hint);
@@ -904,10 +915,8 @@ static int iterate_bicgstab2(wfa_grid* g, const Launch<T>& L, T* x, T** r, T* rh
     }
     if (resident) {
       const int m = resident_chunk(g, h->maxit - h->iter + 1);
-      T* const rb[2] = {r[0], r[1]};
-      T* const pb[2] = {p[0], p[1]};
-      T* const vb[2] = {v[0], v[1]};
-      const hipError_t e = launch_resident<T>(L, kResidentBicgstab2, x, rb, rh, pb, vb, t, m, par);
+      const ResidentVectors<T> vec{x, rh, t, {r[0], r[1]}, {p[0], p[1]}, {v[0], v[1]}};
+      const hipError_t e = launch_resident<T>(L, kResidentBicgstab2, vec, m, par);
       if (e != hipSuccess)
         return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
       par ^= m & 1;
@@ -941,11 +950,22 @@ static int iterate_bicgstab2(wfa_grid* g, const Launch<T>& L, T* x, T** r, T* rh
 }
 
 template <typename T>
-static int iterate_cg(wfa_grid* g, const Launch<T>& L, T* x, T* r, T** d, T* q, Scalars* h,
-                      ChunkTail* tail, int hint) {
+static int iterate_cg(wfa_grid* g, const Launch<T>& L, T* x, T* r, T** d, T* q, T** spare,
+                      Scalars* h, ChunkTail* tail, int hint) {
   int par = 0;
   int rc = WFA_OK;
+  const bool resident = use_resident(g, L, kResidentCg);
   while (h->status == ST_RUN) {
+    if (resident) {
+      const int m = resident_chunk(g, h->maxit - h->iter);
+      const ResidentVectors<T> vec{x, nullptr, q, {r, nullptr}, {d[0], d[1]}, {spare[0], spare[1]}};
+      const hipError_t e = launch_resident<T>(L, kResidentCg, vec, m, par);
+      if (e != hipSuccess)
+        return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
+      par ^= m & 1;
+      if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
+      continue;
+    }
     const int m = next_chunk(g, *h, h->maxit - h->iter, hint);
     int k = 0;
     if (use_graph(g) && m >= kGraphIters) {
@@ -993,10 +1013,8 @@ static int iterate_cg1(wfa_grid* g, const Launch<T>& L, T* x, T** r, T** w, T** 
   while (h->status == ST_RUN) {
     if (resident) {
       const int m = resident_chunk(g, h->maxit - h->iter + (h->stage == 0 ? 1 : 0));
-      T* const rb[2] = {r[0], r[1]};
-      T* const sb[2] = {sv[0], sv[1]};
-      T* const wb[2] = {w[0], w[1]};
-      const hipError_t e = launch_resident<T>(L, kResidentCg1, x, rb, nullptr, sb, wb, p, m, par);
+      const ResidentVectors<T> vec{x, nullptr, p, {r[0], r[1]}, {sv[0], sv[1]}, {w[0], w[1]}};
+      const hipError_t e = launch_resident<T>(L, kResidentCg1, vec, m, par);
       if (e != hipSuccess)
         return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
       par ^= m & 1;
@@ -1106,7 +1124,7 @@ static int solve_plain(wfa_grid* g, const T* b_user, T* x, bool form_b, double t
   ChunkTail* tp = use_tail ? &tail : nullptr;
   const int hint = g->hint_iters;
   if (g->method == WFA_METHOD_CG) {
-    rc = iterate_cg<T>(g, L, x, r, p, t, &h, tp, hint);
+    rc = iterate_cg<T>(g, L, x, r, p, t, v, &h, tp, hint);
   } else if (g->method == WFA_METHOD_CG1) {
     T* w[2] = {v[0], v[1]};
     rc = iterate_cg1<T>(g, L, x, rbuf, w, p, t, &h, tp, hint);
@@ -1114,7 +1132,7 @@ static int solve_plain(wfa_grid* g, const T* b_user, T* x, bool form_b, double t
   else if (g->method == WFA_METHOD_BICGSTAB2)
     rc = iterate_bicgstab2<T>(g, L, x, rbuf, rh, p, v, t, b, &h, &restarts, &rpar, true, tp, hint);
   else
-    rc = iterate_bicgstab<T>(g, L, x, r, rh, p, v, t, b, &h, &restarts, true, tp, hint);
+    rc = iterate_bicgstab<T>(g, L, x, r, vec[8], rh, p, v, t, b, &h, &restarts, true, tp, hint);
   if (rc) return rc;
   g->hint_iters = h.status == ST_CONV && restarts == 0 ? h.iter : 0;
   int status;

@@ -22,7 +22,7 @@ struct Tiling {
 // registers: at most one tile per CU, of two rows per wave and few planes.
 constexpr int kTileOrderRows = 2;
 constexpr int kResidentTiles = 256;
-constexpr int kResidentPlanes = 4;
+constexpr int resident_planes(int elem_bytes) { return elem_bytes == 4 ? 16 : 8; }
 
 Tiling make_tiling(int nx, int ny, int nz, int elem_bytes, int zc_override, int ry_override);
 
@@ -127,13 +127,25 @@ hipError_t launch_persistent_bicgstab(const Launch<T>& L, T* x, T* r, const T* r
 // Resident iterations of small grids (one cooperative launch per chunk, the
 // vectors in registers; the iterates bitwise those of the per-pass
 // launches).  r, p, v: the double-buffered pairs, those of `parity` in.
-enum ResidentKind { kResidentBicgstab2 = 0, kResidentCg1 = 1 };
+enum ResidentKind {
+  kResidentBicgstab = 0, kResidentBicgstab2 = 1, kResidentCg = 2, kResidentCg1 = 3
+};
+// Which of its vectors each method passes as what: CG p = directions, t = q
+// (not kept), v two spare vectors; CG with one reduction p = s, v = w, t = p;
+// textbook BiCGStab and CG have one residual vector, r[0] (BiCGStab: r[1] spare).
+template <typename T>
+struct ResidentVectors {
+  T* x;
+  const T* rh;
+  T* t;
+  T *r[2], *p[2], *v[2];
+};
 int ring_copies(size_t doubles, int ntiles);
 template <typename T>
 bool resident_fits(const Launch<T>& L, int kind);
 template <typename T>
-hipError_t launch_resident(const Launch<T>& L, int kind, T* x, T* const (&r)[2], const T* rh,
-                           T* const (&p)[2], T* const (&v)[2], T* t, int iters, int parity);
+hipError_t launch_resident(const Launch<T>& L, int kind, const ResidentVectors<T>& v, int iters,
+                           int parity);
 // launch_set_scalars, and the ring of a grid of `ntiles` tiles emptied
 void launch_set_resident(Scalars* dst, const Scalars& v, double* ring, int copies, int ntiles,
                          hipStream_t s);

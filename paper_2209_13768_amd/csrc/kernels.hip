@@ -383,9 +383,8 @@ Tiling make_tiling(int nx, int ny, int nz, int elem_bytes, int zc_override, int 
   // is too few (161x97x113, 312 tiles: 107 -> 116 us).  zc >= 2: so many
   // tiles' sums fit a persistent launch's regions.
   t.tile_order = t.ry == kTileOrderRows &&
-                 ((g.ntiles <= kResidentTiles && g.zc <= kResidentPlanes) ||
+                 ((g.ntiles <= kResidentTiles && g.zc <= resident_planes(elem_bytes)) ||
                   (g.ntiles >= 1024 && g.zc >= 2));
-  (void)elem_bytes;
   return t;
 }
 
