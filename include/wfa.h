@@ -283,9 +283,9 @@ enum {
                                   -1: graphs for grids up to 2^23 cells        */,
   WFA_OPT_EXPLICIT_FUSE = 11   /* explicit steps per pass over memory in
                                   wfa_explicit_step: 1 to 4; 0 = automatic
-                                  (with a constant diffusivity 3 in FP32 and
-                                  2 in FP64, else 1).  More than 1 needs
-                                  WFA_COEF_CONST                               */,
+                                  (with a constant diffusivity by grid size,
+                                  up to 4 in FP32 and 3 in FP64, else 1).  More
+                                  than 1 needs WFA_COEF_CONST                  */,
   WFA_OPT_SHADOW = 12,         /* shadow residual of the two-reduction
                                   BiCGStab (also the inner solve of
                                   WFA_F32_IR64): 0 = r0, stored (default); 1 =

@@ -142,6 +142,21 @@ int validate_coeffs(int nx, int ny, int nz, const wfa_coeffs* c) {
   return WFA_OK;
 }
 
+// Rows per wave and z planes per workgroup (0 = default rule) of every
+// stencil pass of the grid.
+void apply_tiling(wfa_grid* g, int ry, int zc) {
+  g->ry = ry;
+  g->zchunk = zc;
+  const int w = g->prec == WFA_F32 ? 4 : 8;
+  g->tl = make_tiling(g->nx, g->ny, g->nz, w, zc, ry);
+  g->tl32 = make_tiling(g->nx, g->ny, g->nz, 4, zc, ry);
+  const Geo& geo = g->tl.geo;
+  g->tl_pass = zc ? g->tl
+                  : make_tiling(g->nx, g->ny, g->nz, w,
+                                pass_planes((long long)geo.tiles_x * geo.tiles_y, g->nz, 2, 16), ry);
+  ++g->graphs.generation;
+}
+
 void grid_setup(wfa_grid* g, int nx, int ny, int nz, const wfa_coeffs* c, char* ws) {
   g->nx = nx; g->ny = ny; g->nz = nz;
   g->n = (size_t)nx * ny * nz;
@@ -163,31 +178,17 @@ void grid_setup(wfa_grid* g, int nx, int ny, int nz, const wfa_coeffs* c, char* 
   g->profile = 0;
   g->force_bd = 0;
   g->check_every = 0;
-  g->zchunk = 0;
   g->ir_inner_tol = 1e-4;
   g->force_div = 0;
   g->hint_iters = 0;
-  const int w = g->prec == WFA_F32 ? 4 : 8;
-  g->ry = 0;
   g->jacobi = 0;
   g->graph = 0;
   g->fuse = 0;
   g->shadow = 0;
   g->recompute_t = 0;
-  g->tl = make_tiling(nx, ny, nz, w, 0, 0);
-  g->tl32 = make_tiling(nx, ny, nz, 4, 0, 0);
+  apply_tiling(g, 0, 0);
 }
 
-// Rows per wave and z planes per workgroup (0 = default rule) of every
-// stencil pass of the grid.
-void apply_tiling(wfa_grid* g, int ry, int zc) {
-  g->ry = ry;
-  g->zchunk = zc;
-  const int w = g->prec == WFA_F32 ? 4 : 8;
-  g->tl = make_tiling(g->nx, g->ny, g->nz, w, zc, ry);
-  g->tl32 = make_tiling(g->nx, g->ny, g->nz, 4, zc, ry);
-  ++g->graphs.generation;
-}
 
 }  // namespace wfa
 
@@ -482,6 +483,16 @@ template <typename T>
 static Launch<T> plain_ctx(wfa_grid* g, Scalars* sc, hipStream_t s) {
   Launch<T> L = ctx<T>(g, sc, s);
   L.op.jac = 0;
+  return L;
+}
+
+// Launch context of a pass without reductions (operator product, right-hand
+// side, explicit step): its own planes per workgroup, unless the grid's tile
+// shape was set.
+template <typename T>
+static Launch<T> pass_ctx(wfa_grid* g, hipStream_t s) {
+  Launch<T> L = plain_ctx<T>(g, g->sc, s);
+  L.tl = g->tl_pass;
   return L;
 }
 
@@ -1419,10 +1430,10 @@ extern "C" int wfa_stencil_apply(wfa_grid* g, const void* x, void* y, void* stre
   hipStream_t s = (hipStream_t)stream;
   if (g->prec == WFA_F32) {
     ProfScope ps(g, WFA_K_APPLY, s);
-    launch_apply<float>(plain_ctx<float>(g, g->sc, s), (const float*)x, (float*)y);
+    launch_apply<float>(pass_ctx<float>(g, s), (const float*)x, (float*)y);
   } else {
     ProfScope ps(g, WFA_K_APPLY, s);
-    launch_apply<double>(plain_ctx<double>(g, g->sc, s), (const double*)x, (double*)y);
+    launch_apply<double>(pass_ctx<double>(g, s), (const double*)x, (double*)y);
   }
   return check_launch("apply");
 }
@@ -1432,9 +1443,9 @@ extern "C" int wfa_rhs(wfa_grid* g, const void* T, void* b, void* stream) {
   if (!T || !b) return set_error(WFA_ERR_INVALID, "T and b must be non-NULL");
   hipStream_t s = (hipStream_t)stream;
   if (g->prec == WFA_F32)
-    launch_rhs<float>(plain_ctx<float>(g, g->sc, s), (const float*)T, (float*)b);
+    launch_rhs<float>(pass_ctx<float>(g, s), (const float*)T, (float*)b);
   else
-    launch_rhs<double>(plain_ctx<double>(g, g->sc, s), (const double*)T, (double*)b);
+    launch_rhs<double>(pass_ctx<double>(g, s), (const double*)T, (double*)b);
   return check_launch("rhs");
 }
 
@@ -1446,14 +1457,25 @@ extern "C" int wfa_explicit_step(wfa_grid* g, void* T, int nsteps, void* stream)
   hipStream_t s = (hipStream_t)stream;
   const size_t w = g->prec == WFA_F32 ? 4 : 8;
   void* bufs[2] = {T, g->vec[0]};
-  // automatic: the fastest measured on 512x512x1024 (FP32 3 steps per pass,
-  // 1.29x one step per pass; FP64 2 steps, 1.32x); one step with a per-cell
-  // diffusivity
-  const int fuse = g->fuse > 0 ? g->fuse
-                   : (g->c.mode != WFA_COEF_CONST ? 1 : (g->prec == WFA_F32 ? 3 : 2));
-  int pass = 0;
-  for (int done = 0; done < nsteps; ++pass) {
-    const int k = nsteps - done >= fuse ? fuse : 1;
+  // Automatic steps per pass with a constant diffusivity (one with a
+  // diffusivity per cell): the fastest measured by grid size.  Small grids are
+  // bound by a workgroup's chain of planes, to which a fused pass adds 2S.
+  // us a step with 1, 2, 3, 4 steps per pass: FP32 128^3 8.4, 9.3, 9.3, 12.5;
+  // 160^3 13.0, 10.4, 13.1, 13.5; 256^3 34, 28, 28, 30; 400^3 122, 75, 67, 72;
+  // 512x512x1024 439, 323, 243, 234.  FP64 128^3 10.8, 12.9, 12.7, 13.3; 160^3
+  // 20.6, 14.7, 14.5, 19.6; 256^3 58, 42, 42, 49; 512^3 427, 252, 220, 257.
+  int fuse = g->fuse;
+  if (fuse == 0) {
+    if (g->c.mode != WFA_COEF_CONST || g->n < ((size_t)3 << 20)) fuse = 1;
+    else if (g->prec != WFA_F32) fuse = 3;
+    else fuse = g->n < ((size_t)40 << 20) ? 2 : g->n < ((size_t)100 << 20) ? 3 : 4;
+  }
+  // The passes alternate between T and the second time level: an even number
+  // of them, where the steps can be shared out so, ends in T without a copy.
+  int passes = nsteps / fuse + (nsteps % fuse ? 1 : 0);
+  if ((passes & 1) && passes < nsteps && fuse > 1) ++passes;
+  for (int pass = 0; pass < passes; ++pass) {
+    const int k = nsteps / passes + (pass < nsteps % passes ? 1 : 0);
     const void* in = bufs[pass & 1];
     void* out = bufs[(pass + 1) & 1];
     if (k > 1) {
@@ -1467,15 +1489,14 @@ extern "C" int wfa_explicit_step(wfa_grid* g, void* T, int nsteps, void* stream)
     } else {
       ProfScope ps(g, WFA_K_EXPLICIT, s);
       if (g->prec == WFA_F32)
-        launch_explicit<float>(plain_ctx<float>(g, g->sc, s), (const float*)in, (float*)out);
+        launch_explicit<float>(pass_ctx<float>(g, s), (const float*)in, (float*)out);
       else
-        launch_explicit<double>(plain_ctx<double>(g, g->sc, s), (const double*)in, (double*)out);
+        launch_explicit<double>(pass_ctx<double>(g, s), (const double*)in, (double*)out);
     }
-    done += k;
   }
   int rc = check_launch("explicit");
   if (rc) return rc;
-  if (pass & 1) HIP_TRY(hipMemcpyAsync(T, bufs[1], w * g->n, hipMemcpyDeviceToDevice, s));
+  if (passes & 1) HIP_TRY(hipMemcpyAsync(T, bufs[1], w * g->n, hipMemcpyDeviceToDevice, s));
   return WFA_OK;
 }
 

@@ -103,6 +103,7 @@ struct wfa_grid {
   wfa::Op<float> op32;
   wfa::Tiling tl;        // tiling of the grid's vector type
   wfa::Tiling tl32;      // tiling of FP32 inner vectors
+  wfa::Tiling tl_pass;   // tiling of the passes without reductions
   int method, persistent, profile, force_bd, check_every, zchunk, ry, jacobi, graph, fuse;
   int shadow;  // two-reduction BiCGStab: 0 r^ = r0 (stored), 1 index-hashed r^
   int recompute_t;  // two-reduction BiCGStab: pass 1 forms t = A s again (not stored)

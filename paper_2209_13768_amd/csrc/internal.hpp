@@ -24,6 +24,11 @@ constexpr int kTileOrderRows = 2;
 constexpr int kResidentTiles = 256;
 constexpr int resident_planes(int elem_bytes) { return elem_bytes == 4 ? 16 : 8; }
 
+// Planes per workgroup of a pass without reductions, whose tiles may be cut
+// freely: `columns` workgroups per z layer, `halo` planes computed or loaded
+// again per workgroup, at most `cap` planes.
+int pass_planes(long long columns, int nz, int halo, int cap);
+
 Tiling make_tiling(int nx, int ny, int nz, int elem_bytes, int zc_override, int ry_override);
 
 // Pointers of one phase launch.

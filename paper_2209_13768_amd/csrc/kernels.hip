@@ -339,6 +339,27 @@ void launch_fill(size_t n, T* y, T v, hipStream_t s) {
 // ============================================================================
 // tiling
 // ============================================================================
+// A workgroup's time goes with its planes, zc + halo, and W workgroups run at a
+// rate that goes as W / (W + 500) (fitted to the fused explicit pass: 73, 171,
+// 196, 267 and 299 planes per us at 192, 480, 800, 1600 and 2800 workgroups).
+// So the pass takes (zc + halo) (W + 500), smallest among powers of two.
+// Against the reducing passes' rule, one explicit step per pass, us: 96^3 FP32
+// 12.3 -> 7.0, 160^3 FP64 24.7 -> 20.6, 512^3 FP64 448 -> 427.
+int pass_planes(long long columns, int nz, int halo, int cap) {
+  int best = 1;
+  double least = 0.0;
+  for (int zc = 1; zc <= cap; zc *= 2) {
+    const double w = (double)columns * ((nz + zc - 1) / zc);
+    const double cost = (zc + halo) * (w + 500.0);
+    if (zc == 1 || cost < least) {
+      best = zc;
+      least = cost;
+    }
+    if (zc >= nz) break;
+  }
+  return best < nz ? best : nz;
+}
+
 Tiling make_tiling(int nx, int ny, int nz, int elem_bytes, int zc_override, int ry_override) {
   Tiling t{};
   // 2 rows per wave (8-row tiles) measured fastest on 256^3 FP64 and
