@@ -614,14 +614,14 @@ static int next_chunk(const wfa_grid* g, const Scalars& h, int budget, int hint)
   } else if (h.iter == 0 && hint > 0) {
     m = hint;
   } else if (h.iter == 0 || !(h.rr > 0.0) || !(h.rr0 > 0.0) || h.rr >= h.rr0) {
-    m = 8;
+    // no estimate: more as the solve goes on, a quarter of it at most wasted
+    m = h.iter < 480 ? 8 + h.iter / 4 : 128;
   } else {
     const double rate = log(h.rr / h.rr0) / (double)h.iter;  // < 0
-    const double target = log(h.tol * h.tol * h.bb);
+    const double target = 2.0 * log(h.tol) + log(h.bb);      // (tol^2 may underflow)
     double rem = (target - log(h.rr)) / rate;
     if (!(rem > 0.0)) rem = 1.0;
-    m = (int)ceil(rem * 1.05) + 1;
-    if (m > 512) m = 512;
+    m = rem < 480.0 ? (int)ceil(rem * 1.05) + 1 : 512;
   }
   if (m > budget) m = budget;
   if (m < 1) m = 1;
