@@ -178,6 +178,56 @@ __device__ __forceinline__ T cell_apply(const Op<T>& op, T c, const T nb[6], T k
   return cell_apply<T, CELL, FORM>(op, c, nb, kP, kN, inside, dg, kz, false);
 }
 
+// cell_apply where the y and z neighbours all exist (a wave's rows and plane
+// say so for all its lanes) and, with XIN, the x neighbours too: the same
+// operations without a branch per face, so that a thread's rows and their
+// faces are in flight together.  ix0, ix1: the x neighbours exist.  CARRY: the
+// z- face's harmonic mean is kz (see cell_apply).
+template <typename T, bool CELL, int FORM, bool XIN, bool CARRY>
+__device__ __forceinline__ T cell_apply_inner(const Op<T>& op, T c, const T nb[6], T kP,
+                                              const T kN[6], bool ix0, bool ix1, T& dg, T& kz) {
+#pragma clang fp contract(off)
+  constexpr bool CONV = FORM != kFormDiffusion;
+  T diag = T(1), acc = T(0);
+#pragma unroll
+  for (int f = 0; f < 6; ++f) {
+    T d_out, d_in;
+    if (CELL) {
+      const T kf = (f == 4 && CARRY) ? kz : T(2) * kP * kN[f] * pos_rcp(kP + kN[f]);
+      if (f == 5) kz = kf;
+      if (CONV) {
+        d_out = fma_t(op.cD, kf, op.out[f]);
+        d_in = fma_t(op.cD, kf, op.in[f]);
+      } else {
+        d_out = d_in = op.cD * kf;
+      }
+    } else if (CONV) {
+      d_out = op.cD + op.out[f];
+      d_in = op.cD + op.in[f];
+    } else {
+      d_out = d_in = op.cD;
+    }
+    if (f < 2 && !XIN) {
+      const bool in = f == 0 ? ix0 : ix1;
+      T edge = T(0);   // diag + 0 is diag
+      if (op.dir & (1u << f)) {
+        if (CONV) edge = CELL ? fma_t(op.cD, kP, op.out[f]) : op.cD + op.out[f];
+        else edge = CELL ? op.cD * kP : op.cD;
+      }
+      diag += in ? d_out : edge;
+      const T with = fma_t(d_in, nb[f], acc);
+      acc = in ? with : acc;
+    } else {
+      diag += d_out;
+      acc = fma_t(d_in, nb[f], acc);
+    }
+  }
+  dg = diag;
+  const T y = fma_t(diag, c, -acc);
+  if (FORM != kFormGeneral) return y;
+  return op.jac ? y * pos_rcp(diag) : y;
+}
+
 // The diffusion-only operator (op_form(op) == kFormDiffusion, per-cell
 // diffusivity) split into its coefficients and their application, for a
 // pass that applies A to two vectors on the same cells: D[f] = cD
@@ -534,10 +584,9 @@ struct carry_z<Ph, std::void_t<decltype(Ph::kCarryZ)>> {
 };
 
 template <typename T, bool CELL, int RY, class Ph, int FORM = kFormGeneral>
-__device__ __forceinline__ void march_tile(const Geo& g, const Op<T>& op,
-                                           const float* __restrict__ kappa, int tile,
-                                           Ph& ph, double (&acc)[Ph::NV], T* su,
-                                           float* sk) {
+__device__ __forceinline__ void march_tile_lanes(const Geo& g, const Op<T>& op,
+                                                 const float* __restrict__ kappa, int tile, Ph& ph,
+                                                 double (&acc)[Ph::NV], T* su, float* sk) {
   using TS = TileShape<RY>;
   constexpr int TY = TS::TY, LW = TS::LW, LH = TS::LH;
   constexpr int PD = Ph::PD;  // planes of loads in flight ahead of the compute
@@ -758,6 +807,320 @@ __device__ __forceinline__ void march_tile(const Geo& g, const Op<T>& op,
     }
   }
   __syncthreads();  // LDS planes are reused by the next tile of this workgroup
+}
+
+// The same engine with the tests for the grid's edges made by waves instead of
+// lanes.  In march_tile_lanes every load, face and row of a cell stands behind
+// its own branch, which keeps the registers low but puts what they enclose in
+// series; here a plane's loads and both rows' faces are in flight together.
+// It pays in the passes with many streams and where the operator's rows are
+// cheap, and costs the FP64 passes with few streams and a diffusivity per
+// cell their occupancy (Ph::kWaveTests; us per pass, by lanes -> by waves):
+//   PhAC   128^3 FP64 52 -> 46, 256^3 FP64 264 -> 251, per cell 262 -> 259;
+//          FP32 128^3 per cell 38 -> 32, 512x512x256 544 -> 496; per cell with
+//          convection or scaling 142 VGPRs and 3 waves per SIMD, or 4 and
+//          60 B of scratch: 192^3 74 -> 90: lanes
+//   PhA    FP32 256^3 per cell 145 -> 102   (FP64 per cell 180 -> 189: lanes)
+//   PhCg1  FP64 128^3 per cell 64 -> 43     (FP32 256^3 151 -> 157: lanes)
+//   PhResid of FP32 fields 512x512x256 400 -> 199   (per cell: lanes)
+//   PhApply, PhExplicit 192^3 FP64 28 -> 23, 31 -> 29 (per cell 86 -> 97: lanes)
+//   PhB2   per cell FP64 256^3 106 -> 132, FP32 512x512x256 237 -> 255: lanes
+template <typename T, bool CELL, int RY, class Ph, int FORM = kFormGeneral>
+__device__ __forceinline__ void march_tile_waves(const Geo& g, const Op<T>& op,
+                                                 const float* __restrict__ kappa, int tile, Ph& ph,
+                                                 double (&acc)[Ph::NV], T* su, float* sk) {
+  using TS = TileShape<RY>;
+  constexpr int TY = TS::TY, LW = TS::LW, LH = TS::LH;
+  constexpr int PD = Ph::PD;  // planes of loads in flight ahead of the compute
+  static_assert(PD == 1 || PD == 2, "prefetch depth 1 or 2");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tx = tile % g.tiles_x;
+  const int rest = tile / g.tiles_x;
+  const int ty = rest % g.tiles_y;
+  const int tz = rest / g.tiles_y;
+  const int x0 = tx * kTX, y0 = ty * TY;
+  const int k0 = tz * g.zc;
+  const int k1 = min(k0 + g.zc, g.nz);
+  const int nx = g.nx, ny = g.ny, nz = g.nz;
+  const size_t plane = (size_t)g.plane;
+
+  // Own cells.  A thread without one (right of or below the grid) loads its
+  // plane's first cell and computes along; its results are stored and summed
+  // nowhere.  What a whole wave has in common -- its rows lie in the grid
+  // (full), none on a y face (y_in), no lane on an x face (x_in) -- is tested
+  // once for the wave.
+  const int i = x0 + lane, jw = y0 + wave * RY;
+  bool own[RY];
+  int poff[RY];      // offset inside a plane
+  int lidx[RY];      // LDS index
+  uint32_t ins_xy[RY];
+#pragma unroll
+  for (int r = 0; r < RY; ++r) {
+    const int j = jw + r;
+    own[r] = (i < nx) && (j < ny);
+    poff[r] = own[r] ? i + nx * j : 0;
+    lidx[r] = (wave * RY + r + 1) * LW + lane + 1;
+    ins_xy[r] = (i > 0 ? 1u : 0u) | (i < nx - 1 ? 2u : 0u) | (j > 0 ? 4u : 0u) |
+                (j < ny - 1 ? 8u : 0u);
+  }
+  const bool full = x0 + kTX <= nx && jw + RY <= ny;
+  const bool y_in = jw > 0 && jw + RY < ny;
+  const bool x_in = x0 > 0 && x0 + kTX < nx;
+  const bool ix0 = i > 0, ix1 = i < nx - 1;
+  // halo cell of this thread
+  int hl = -1, hoff = 0;
+  bool hval = false;
+  {
+    const int hs = threadIdx.x;
+    int hi = 0, hj = 0;
+    if (hs < kTX) { hi = x0 + hs; hj = y0 - 1; hl = hs + 1; }
+    else if (hs < 2 * kTX) { hi = x0 + hs - kTX; hj = y0 + TY; hl = (LH - 1) * LW + hs - kTX + 1; }
+    else if (hs < 2 * kTX + TY) { hi = x0 - 1; hj = y0 + hs - 2 * kTX; hl = (hs - 2 * kTX + 1) * LW; }
+    else if (hs < TS::NHALO) { hi = x0 + kTX; hj = y0 + hs - 2 * kTX - TY; hl = (hs - 2 * kTX - TY + 1) * LW + LW - 1; }
+    if (hl >= 0) {
+      hval = hi >= 0 && hi < nx && hj >= 0 && hj < ny;
+      hoff = hval ? hi + nx * hj : 0;
+    }
+  }
+  // f(r) for the rows of this thread that are cells of the grid
+  auto each_own = [&](auto f) {
+    if (full) {
+#pragma unroll
+      for (int r = 0; r < RY; ++r) f(r);
+    } else {
+#pragma unroll
+      for (int r = 0; r < RY; ++r)
+        if (own[r]) f(r);
+    }
+  };
+
+  using Raw = typename Ph::Raw;
+  using ORaw = typename Ph::ORaw;
+  using ERaw = typename Ph::ERaw;
+  // Loads of one plane that are in flight: own cells' stage inputs and
+  // diffusivity, the halo cell's, and the epilogue's inputs.
+  struct PlaneLoads {
+    ORaw o[RY];
+    float ko[RY];
+    Raw h;
+    float kh;
+    ERaw e[RY];
+  };
+  // Issue the loads of plane kp (stage inputs up to the z-halo plane k1,
+  // halo and epilogue inputs for output planes only).
+  auto issue = [&](PlaneLoads& S, int kp) {
+    if (kp > k1 || kp >= nz) return;
+    const size_t base = (size_t)kp * plane;
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      S.o[r] = ph.fetch_own(base + poff[r]);
+      if (CELL) S.ko[r] = kappa[base + poff[r]];
+    }
+    if (kp == k1) return;
+#pragma unroll
+    for (int r = 0; r < RY; ++r) S.e[r] = ph.efetch(base + poff[r]);
+    if (hval) {
+      S.h = ph.fetch(base + hoff);
+      if (CELL) S.kh = kappa[base + hoff];
+    }
+  };
+
+  using St = typename Ph::St;  // staged value (and what the epilogue needs of it)
+  T up[RY];
+  St uc[RY];
+  float kpv[RY], kcv[RY];   // diffusivity stays FP32 (as stored) until used
+  T hc = T(0);
+  float kh = 1.f;
+  ERaw ec[RY];
+  // A phase that opts in (kCarryZ) carries each cell's z+ face coefficient
+  // to the next plane's z- face: one harmonic mean less per cell, the same
+  // value bit for bit.  It pays in the passes with few streams; in the
+  // fused update pass the extra registers cost more than it saves.
+  constexpr bool CZ = carry_z<Ph>::value;
+  T kz[RY];                 // z- face coefficient of the plane to compute
+#pragma unroll
+  for (int r = 0; r < RY; ++r) kz[r] = T(0);
+
+  // plane k0 - 1 (own cells only) and plane k0 (own + halo), staged directly
+#pragma unroll
+  for (int r = 0; r < RY; ++r) {
+    up[r] = T(0);
+    kpv[r] = kcv[r] = 1.f;
+    uc[r] = St{};
+  }
+  if (k0 > 0) {
+    const size_t base = (size_t)(k0 - 1) * plane;
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      up[r] = Ph::val(ph.combine(ph.fetch(base + poff[r])));
+      if (CELL) kpv[r] = kappa[base + poff[r]];
+    }
+  }
+  {
+    const size_t base = (size_t)k0 * plane;
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      ec[r] = ph.efetch(base + poff[r]);
+      if (CELL) kcv[r] = kappa[base + poff[r]];
+    }
+    if (hval) {
+      hc = Ph::val(ph.combine(ph.fetch(base + hoff)));
+      if (CELL) kh = kappa[base + hoff];
+    }
+    each_own([&](int r) {
+      const size_t idx = base + poff[r];
+      uc[r] = ph.combine_own(ph.fetch_own(idx), idx, acc);
+    });
+  }
+  if constexpr (CELL && CZ) {
+#pragma unroll
+    for (int r = 0; r < RY; ++r)
+      kz[r] = T(2) * (T)kcv[r] * (T)kpv[r] * pos_rcp((T)kcv[r] + (T)kpv[r]);
+  }
+  PlaneLoads L0, L1;
+  issue(L0, k0 + 1);
+  if (PD == 2) issue(L1, k0 + 2);
+
+  int buf = 0;
+  // One output plane k; S holds the loads of plane k+1 and is refilled
+  // with plane k+1+PD.
+  auto step = [&](int k, PlaneLoads& S) {
+    T* Lu = su + buf * (LH * LW);
+    float* Lk = CELL ? sk + buf * (LH * LW) : nullptr;
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      Lu[lidx[r]] = Ph::val(uc[r]);
+      if (CELL) Lk[lidx[r]] = kcv[r];
+    }
+    if (hl >= 0) {
+      Lu[hl] = hval ? hc : T(0);
+      if (CELL) Lk[hl] = hval ? kh : 1.f;
+    }
+    __syncthreads();
+
+    // stage plane k + 1 from its (now due) loads; an output plane's own
+    // cells go through combine_own (which may store and accumulate), the
+    // z-halo plane k1 only yields the stencil value
+    St un[RY];
+    T unv[RY];
+    float knv[RY];
+    ERaw en[RY];
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      un[r] = St{};
+      unv[r] = T(0);
+      knv[r] = 1.f;
+      en[r] = S.e[r];
+    }
+    T hn = T(0);
+    float khn = 1.f;
+    if (k + 1 < k1) {
+      each_own([&](int r) {
+        un[r] = ph.combine_own(S.o[r], (size_t)(k + 1) * plane + poff[r], acc);
+        unv[r] = Ph::val(un[r]);
+      });
+      if (hval) {
+        hn = Ph::val(ph.combine(S.h));
+        if (CELL) khn = S.kh;
+      }
+    } else if (k + 1 < nz) {
+#pragma unroll
+      for (int r = 0; r < RY; ++r) unv[r] = ph.value_own(S.o[r]);
+    }
+    if (CELL && k + 1 < nz) {
+#pragma unroll
+      for (int r = 0; r < RY; ++r) knv[r] = S.ko[r];
+    }
+    issue(S, k + 1 + PD);
+
+    // compute plane k
+    T Au[RY], dg[RY];
+    T nb[RY][6], kn6[RY][6];
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      const int l = lidx[r];
+      nb[r][0] = Lu[l - 1]; nb[r][1] = Lu[l + 1];
+      nb[r][2] = Lu[l - LW]; nb[r][3] = Lu[l + LW];
+      nb[r][4] = up[r]; nb[r][5] = unv[r];
+      if (CELL) {
+        kn6[r][0] = (T)Lk[l - 1]; kn6[r][1] = (T)Lk[l + 1];
+        kn6[r][2] = (T)Lk[l - LW]; kn6[r][3] = (T)Lk[l + LW];
+        kn6[r][4] = (T)kpv[r]; kn6[r][5] = (T)knv[r];
+      } else {
+#pragma unroll
+        for (int f = 0; f < 6; ++f) kn6[r][f] = T(1);
+      }
+    }
+    if (y_in && k > 0 && k < nz - 1) {
+      if (x_in) {
+#pragma unroll
+        for (int r = 0; r < RY; ++r)
+          Au[r] = cell_apply_inner<T, CELL, FORM, true, CZ>(op, Ph::val(uc[r]), nb[r], (T)kcv[r],
+                                                            kn6[r], true, true, dg[r], kz[r]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < RY; ++r)
+          Au[r] = cell_apply_inner<T, CELL, FORM, false, CZ>(op, Ph::val(uc[r]), nb[r], (T)kcv[r],
+                                                             kn6[r], ix0, ix1, dg[r], kz[r]);
+      }
+    } else {
+      const uint32_t ins_z = (k > 0 ? 16u : 0u) | (k < nz - 1 ? 32u : 0u);
+#pragma unroll
+      for (int r = 0; r < RY; ++r) {
+        if constexpr (CZ)
+          Au[r] = cell_apply<T, CELL, FORM>(op, Ph::val(uc[r]), nb[r], (T)kcv[r], kn6[r],
+                                            ins_xy[r] | ins_z, dg[r], kz[r], true);
+        else
+          Au[r] = cell_apply<T, CELL, FORM>(op, Ph::val(uc[r]), nb[r], (T)kcv[r], kn6[r],
+                                            ins_xy[r] | ins_z, dg[r]);
+      }
+    }
+    const uint32_t ins_z = (k > 0 ? 16u : 0u) | (k < nz - 1 ? 32u : 0u);
+    each_own([&](int r) {
+      ph.epilogue((size_t)k * plane + poff[r], uc[r], Au[r], (T)kcv[r], ins_xy[r] | ins_z, ec[r],
+                  dg[r], acc);
+    });
+    // rotate
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      up[r] = Ph::val(uc[r]); uc[r] = un[r];
+      kpv[r] = kcv[r]; kcv[r] = knv[r];
+      ec[r] = en[r];
+    }
+    hc = hn; kh = khn;
+    buf ^= 1;
+  };
+
+  for (int k = k0; k < k1;) {
+    step(k, L0);
+    ++k;
+    if (PD == 2 && k < k1) {
+      step(k, L1);
+      ++k;
+    }
+  }
+  __syncthreads();  // LDS planes are reused by the next tile of this workgroup
+}
+
+// Phases say with a member template kWaveTests<CELL, FORM> which engine they
+// take at two rows per wave (the default; four would not fit the registers);
+// the others take the lanes'.
+template <class Ph, bool CELL, int FORM, class = void>
+struct wave_tests { static constexpr bool value = false; };
+template <class Ph, bool CELL, int FORM>
+struct wave_tests<Ph, CELL, FORM, std::void_t<decltype(Ph::template kWaveTests<CELL, FORM>)>> {
+  static constexpr bool value = Ph::template kWaveTests<CELL, FORM>;
+};
+
+template <typename T, bool CELL, int RY, class Ph, int FORM = kFormGeneral>
+__device__ __forceinline__ void march_tile(const Geo& g, const Op<T>& op,
+                                           const float* __restrict__ kappa, int tile, Ph& ph,
+                                           double (&acc)[Ph::NV], T* su, float* sk) {
+  if constexpr (RY == 2 && wave_tests<Ph, CELL, FORM>::value)
+    march_tile_waves<T, CELL, RY, Ph, FORM>(g, op, kappa, tile, ph, acc, su, sk);
+  else
+    march_tile_lanes<T, CELL, RY, Ph, FORM>(g, op, kappa, tile, ph, acc, su, sk);
 }
 
 }  // namespace wfa

@@ -28,11 +28,12 @@ namespace wfa {
 // ============================================================================
 // generic stencil-pass kernel
 // ============================================================================
-// Waves per SIMD a build is compiled for (1: the compiler's choice).  The
-// hashed-shadow builds of the no-scaling operators at two rows per wave fit
-// 5 waves without spilling: the FP64 second pass in 93 VGPRs (98 and 4 waves
-// otherwise; measured 3-4% faster on 256^3), the FP32 fused update pass in
-// 96.
+// Waves per SIMD a build is compiled for (1: the compiler's choice).  At two
+// rows per wave and a diffusivity per cell: the FP64 second pass with a hashed
+// shadow fits 5 waves without spilling, in 93 VGPRs (98 and 4 waves otherwise;
+// measured 3-4% faster on 256^3), and so does the FP32 fused update pass with
+// convection, in 96; without, where it tests by waves, it fits 4 in 128 (130
+// and 3 otherwise).
 template <typename T, bool CELL, int RY, class Ph, int FORM>
 struct MinWaves {
   static constexpr int value = 1;
@@ -43,7 +44,11 @@ struct MinWaves<double, true, 2, PhB2<double, true>, FORM> {
 };
 template <int FORM>
 struct MinWaves<float, true, 2, PhAC<float, true>, FORM> {
-  static constexpr int value = 5;
+  static constexpr int value = FORM == kFormDiffusion ? 4 : 5;
+};
+template <>
+struct MinWaves<float, true, 2, PhAC<float, false>, kFormDiffusion> {
+  static constexpr int value = 4;
 };
 
 template <typename T, bool CELL, int RY, class Ph, class Fin, int FORM = kFormGeneral>
@@ -401,11 +406,12 @@ Tiling make_tiling(int nx, int ny, int nz, int elem_bytes, int zc_override, int 
   // that order.  Grids of four tiles a CU or more gain from its streaming
   // hints and whole rows (textbook BiCGStab per iteration: 256^3 FP64 497 ->
   // 441 us, 512^3 FP32 2350 -> 2264 us); between them a tile per workgroup
-  // is too few (161x97x113, 312 tiles: 107 -> 116 us).  zc >= 2: so many
-  // tiles' sums fit a persistent launch's regions.
+  // is too few (161x97x113, 312 tiles: 107 -> 116 us), and rows that do not
+  // fill the tiles' lanes give the gain back (174x158x392: 5% slower).  zc >=
+  // 2: so many tiles' sums fit a persistent launch's regions.
   t.tile_order = t.ry == kTileOrderRows &&
                  ((g.ntiles <= kResidentTiles && g.zc <= resident_planes(elem_bytes)) ||
-                  (g.ntiles >= 1024 && g.zc >= 2));
+                  (g.ntiles >= 1024 && g.zc >= 2 && nx % kTX == 0));
   return t;
 }
 

@@ -241,6 +241,7 @@ template <typename T>
 struct PhApply {
   static constexpr int NV = 1;
   static constexpr int PD = 1;
+  template <bool CELL, int FORM> static constexpr bool kWaveTests = !CELL;
   using St = T;
   static __device__ __forceinline__ T val(T u) { return u; }
   const T* __restrict__ x;
@@ -285,6 +286,7 @@ template <typename T, bool CELL>
 struct PhExplicit {
   static constexpr int NV = 1;
   static constexpr int PD = 2;
+  template <bool C, int FORM> static constexpr bool kWaveTests = !C;
   using St = T;
   static __device__ __forceinline__ T val(T u) { return u; }
   Op<T> op;
@@ -354,6 +356,7 @@ template <typename T>
 struct PhA {
   static constexpr int NV = 1;
   static constexpr int PD = 1;
+  template <bool CELL, int FORM> static constexpr bool kWaveTests = sizeof(T) == 4 || !CELL;
   using St = StageP<T>;
   static __device__ __forceinline__ T val(const St& u) { return u.p; }
   static __device__ __forceinline__ T val(T u) { return u; }
@@ -463,6 +466,7 @@ template <typename Tin>
 struct PhResid {
   static constexpr int NV = 4;
   static constexpr int PD = 1;
+  template <bool CELL, int FORM> static constexpr bool kWaveTests = sizeof(Tin) == 4 && !CELL;
   using St = double;
   static __device__ __forceinline__ double val(double u) { return u; }
   const Tin* __restrict__ x;
@@ -513,6 +517,8 @@ template <typename T, bool HASHED = false>
 struct PhAC {
   static constexpr int NV = 3;
   static constexpr int PD = 2;  // measured: 4% faster than 1 at 256^3 FP64
+  template <bool CELL, int FORM> static constexpr bool kWaveTests =
+      sizeof(T) == 8 || !CELL || FORM == kFormDiffusion;
   using St = StageP<T>;
   static __device__ __forceinline__ T val(const St& u) { return u.p; }
   static __device__ __forceinline__ T val(T u) { return u; }
@@ -651,6 +657,7 @@ template <typename T>
 struct PhCg1 {
   static constexpr int NV = 2;
   static constexpr int PD = 2;
+  template <bool CELL, int FORM> static constexpr bool kWaveTests = sizeof(T) == 8 || CELL;
   using St = T;
   static __device__ __forceinline__ T val(T u) { return u; }
   const T* __restrict__ r;
