@@ -45,8 +45,8 @@ k_batch_march(const SolveDesc<T>* __restrict__ descs, const int* __restrict__ ba
     ph.r_out = pp ? d.r : d.r1; ph.w_out = pp ? d.v0 : d.v1; ph.s_out = pp ? d.p0 : d.p1;
     ph.bind(sc);
     double acc[2] = {0.0, 0.0};
-    if (d.cell) march_tile<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
-    else march_tile<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+    if (d.cell) march_tile_lanes<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+    else march_tile_lanes<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
     publish_and_finalize<2>(acc, tile, d.geo.ntiles, d.partials, sc, red, FinCg1{sc});
     return;
   }
@@ -64,8 +64,8 @@ k_batch_march(const SolveDesc<T>* __restrict__ descs, const int* __restrict__ ba
     ph.hashed = d.hashed;
     ph.bind(sc);
     double acc[3] = {0.0, 0.0, 0.0};
-    if (d.cell) march_tile<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
-    else march_tile<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+    if (d.cell) march_tile_lanes<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+    else march_tile_lanes<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
     publish_and_finalize<3>(acc, tile, d.geo.ntiles, d.partials, sc, red, FinAC{sc});
   } else {
     PhB2<T> ph{};
@@ -73,10 +73,83 @@ k_batch_march(const SolveDesc<T>* __restrict__ descs, const int* __restrict__ ba
     ph.hashed = d.hashed;
     ph.bind(sc);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (d.cell) march_tile<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
-    else march_tile<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+    if (d.cell) march_tile_lanes<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+    else march_tile_lanes<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
     publish_and_finalize<4>(acc, tile, d.geo.ntiles, d.partials, sc, red, FinB2{sc});
   }
+}
+
+// The same passes for solves that are all two-reduction BiCGStab with a hashed
+// shadow residual and one operator build (batch_build), as a stream of
+// requests of one kind makes them, at two rows per wave.  The mixed build's
+// bound is the waves a SIMD holds and what every item decides again: it
+// carries both kinds of coefficients, both shadows and CG.  A constant
+// diffusivity with Jacobi scaling (the refined requests' inner solves) has 94
+// and 52 VGPRs here against 104 of the mixed build's lanes: 32 heat requests,
+// FP32 inner solves, the update pass 128 -> 101 us and the second 57 -> 48 us
+// on average.  The same tiles, sums and values bit for bit.
+template <typename T, bool CELL, int FORM, int PASS>
+__global__ void __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(
+    MinWaves<T, CELL, 2, std::conditional_t<PASS == 0, PhAC<T, true>, PhB2<T, true>>,
+             FORM>::value)))
+k_batch_uniform(const SolveDesc<T>* __restrict__ descs, const int* __restrict__ bases,
+                int nsolves, int parity) {
+  using TS = TileShape<2>;
+  __shared__ T su[2 * TS::LH * TS::LW];
+  __shared__ float sk[CELL ? 2 * TS::LH * TS::LW : 1];
+  __shared__ double red[kWaves * kMaxReduce];
+  const int s = find_solve(bases, nsolves, blockIdx.x);
+  const SolveDesc<T>& d = descs[s];
+  Scalars* sc = d.sc;
+  if (sc->status != ST_RUN || sc->restart) return;
+  const int tile = blockIdx.x - bases[s];
+  const Geo geo = d.geo;
+  const Op<T> op = d.op;
+  parity ^= d.par;
+  T* r_in = parity ? d.r1 : d.r;
+  T* r_out = parity ? d.r : d.r1;
+  T* v_out = parity ? d.v0 : d.v1;
+  if constexpr (PASS == 0) {
+    PhAC<T, true> ph{};
+    ph.r = r_in; ph.v = parity ? d.v1 : d.v0; ph.t = d.t; ph.p = parity ? d.p1 : d.p0;
+    ph.x = d.x;
+    ph.r_out = r_out; ph.p_out = parity ? d.p0 : d.p1; ph.v_out = v_out;
+    ph.hashed = 1;
+    ph.bind(sc);
+    double acc[3] = {0.0, 0.0, 0.0};
+    march_tile<T, CELL, 2, PhAC<T, true>, FORM>(geo, op, d.kappa, tile, ph, acc, su, sk);
+    publish_and_finalize<3>(acc, tile, geo.ntiles, d.partials, sc, red, FinAC{sc});
+  } else {
+    PhB2<T, true> ph{};
+    ph.r = r_out; ph.v = v_out; ph.t = d.t;
+    ph.hashed = 1;
+    ph.bind(sc);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    march_tile<T, CELL, 2, PhB2<T, true>, FORM>(geo, op, d.kappa, tile, ph, acc, su, sk);
+    publish_and_finalize<4>(acc, tile, geo.ntiles, d.partials, sc, red, FinB2{sc});
+  }
+}
+
+template <typename T>
+int batch_build(const SolveDesc<T>* d, int nsolves, int ry) {
+  if (ry != 2 || nsolves < 1) return kBatchAny;
+  const int form = op_form(d[0].op), cell = d[0].cell;
+  for (int s = 0; s < nsolves; ++s)
+    if (d[s].cg1 || !d[s].hashed || d[s].cell != cell || op_form(d[s].op) != form)
+      return kBatchAny;
+  return 2 * form + cell;
+}
+template int batch_build<float>(const SolveDesc<float>*, int, int);
+template int batch_build<double>(const SolveDesc<double>*, int, int);
+
+template <typename T, bool CELL, int FORM>
+static void batch_uniform2(const SolveDesc<T>* descs, const int* tile_bases, int tiles_total,
+                           int nsolves, int q, hipStream_t s) {
+  hipLaunchKernelGGL((k_batch_uniform<T, CELL, FORM, 0>), dim3(tiles_total), dim3(kThreads), 0, s,
+                     descs, tile_bases, nsolves, q & 1);
+  hipLaunchKernelGGL((k_batch_uniform<T, CELL, FORM, 1>), dim3(tiles_total), dim3(kThreads), 0, s,
+                     descs, tile_bases, nsolves, q & 1);
 }
 
 template <typename T, int RY>
@@ -90,7 +163,19 @@ static void batch_iteration2(const SolveDesc<T>* descs, const int* tile_bases, i
 
 template <typename T>
 void launch_batch_iteration2(const SolveDesc<T>* descs, const int* tile_bases, int tiles_total,
-                             int nsolves, int q, int ry, hipStream_t s) {
+                             int nsolves, int q, int ry, int build, hipStream_t s) {
+#define WFA_BATCH(FORMV)                                                                        \
+  case 2 * FORMV:                                                                               \
+    return batch_uniform2<T, false, FORMV>(descs, tile_bases, tiles_total, nsolves, q, s);      \
+  case 2 * FORMV + 1:                                                                           \
+    return batch_uniform2<T, true, FORMV>(descs, tile_bases, tiles_total, nsolves, q, s)
+  switch (build) {
+    WFA_BATCH(kFormDiffusion);
+    WFA_BATCH(kFormConvection);
+    WFA_BATCH(kFormDiffusionScaled);
+    WFA_BATCH(kFormConvectionScaled);
+  }
+#undef WFA_BATCH
   switch (ry) {
     case 1: batch_iteration2<T, 1>(descs, tile_bases, tiles_total, nsolves, q, s); break;
     case 4: batch_iteration2<T, 4>(descs, tile_bases, tiles_total, nsolves, q, s); break;
@@ -132,8 +217,8 @@ k_batch_persistent(const SolveDesc<T>* __restrict__ descs, const int* __restrict
       ph.hashed = d.hashed;
       ph.bind(sc);
       double acc[3] = {0.0, 0.0, 0.0};
-      if (d.cell) march_tile<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
-      else march_tile<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+      if (d.cell) march_tile_lanes<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+      else march_tile_lanes<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
       block_sum<3>(acc, red);
       store_partial<3>(d.partials, d.geo.ntiles, tile, acc);
     }
@@ -161,8 +246,8 @@ k_batch_persistent(const SolveDesc<T>* __restrict__ descs, const int* __restrict
       ph.hashed = d.hashed;
       ph.bind(sc);
       double acc[4] = {0.0, 0.0, 0.0, 0.0};
-      if (d.cell) march_tile<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
-      else march_tile<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+      if (d.cell) march_tile_lanes<T, true, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
+      else march_tile_lanes<T, false, RY>(d.geo, d.op, d.kappa, tile, ph, acc, su, sk);
       block_sum<4>(acc, red);
       store_partial<4>(d.partials, d.geo.ntiles, tile, acc);
     }
@@ -215,9 +300,9 @@ hipError_t launch_batch_persistent(const SolveDesc<T>* descs, const int* tile_ba
 }
 
 template void launch_batch_iteration2<float>(const SolveDesc<float>*, const int*, int, int, int,
-                                             int, hipStream_t);
+                                             int, int, hipStream_t);
 template void launch_batch_iteration2<double>(const SolveDesc<double>*, const int*, int, int,
-                                              int, int, hipStream_t);
+                                              int, int, int, hipStream_t);
 
 template hipError_t launch_batch_persistent<float>(const SolveDesc<float>*, const int*, int, int,
                                                    int, int, GridBarrier*, int, hipStream_t);

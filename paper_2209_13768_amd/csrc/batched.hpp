@@ -26,6 +26,13 @@ struct SolveDesc {
   int pw_blocks;
 };
 
+// The build of the batched passes for these solves (descriptors in host
+// memory): 2 FORM + CELL where they are all two-reduction BiCGStab with a
+// hashed shadow residual and that operator build, kBatchAny otherwise.
+constexpr int kBatchAny = -1;
+template <typename T>
+int batch_build(const SolveDesc<T>* d, int nsolves, int ry);
+
 // One two-reduction BiCGStab iteration (passes AC and B2) of every solve in
 // descs[0..nsolves), or two iterations of a solve marked cg1.  tile_bases: prefix sums of the solves' tile counts
 // (nsolves + 1 entries, device memory); every solve's tiling must use `ry`
@@ -34,7 +41,7 @@ struct SolveDesc {
 // descriptors were written.
 template <typename T>
 void launch_batch_iteration2(const SolveDesc<T>* descs, const int* tile_bases, int tiles_total,
-                             int nsolves, int q, int ry, hipStream_t s);
+                             int nsolves, int q, int ry, int build, hipStream_t s);
 
 // `iters` such iterations in one cooperative launch, with grid barriers in
 // place of the kernel boundaries (bitwise the same iterates).  `bar` is a

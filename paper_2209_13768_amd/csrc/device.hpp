@@ -82,16 +82,25 @@ struct Op {
   uint32_t conv;   // 1: some face has a convective term (in[f] or out[f] != 0)
 };
 
-// Builds of the cell operator (cell_apply's FORM): the general one, and two
-// that leave out terms an operator does not have -- the Jacobi scaling
-// select, and also the convective terms -- for fewer vector instructions.
-// Each gives the general build's values bit for bit on the operators it is
-// chosen for (op_form).
-enum OpForm : int { kFormDiffusion = 0, kFormConvection = 1, kFormGeneral = 2 };
+// Builds of the cell operator (cell_apply's FORM): the general one, which
+// looks at the operator's flags, and one for each of their combinations --
+// with the convective terms or without, Jacobi-scaled or not -- with fewer
+// vector instructions and registers.  Each gives the general build's values
+// bit for bit on the operators it is chosen for (op_form).
+enum OpForm : int {
+  kFormDiffusion = 0, kFormConvection = 1, kFormGeneral = 2, kFormDiffusionScaled = 3,
+  kFormConvectionScaled = 4
+};
+constexpr bool form_conv(int form) {
+  return form != kFormDiffusion && form != kFormDiffusionScaled;
+}
+constexpr bool form_scaled(int form) {
+  return form == kFormDiffusionScaled || form == kFormConvectionScaled;
+}
 
 template <typename T>
 __host__ __device__ inline int op_form(const Op<T>& op) {
-  if (op.jac) return kFormGeneral;
+  if (op.jac) return op.conv ? kFormConvectionScaled : kFormDiffusionScaled;
   return op.conv ? kFormConvection : kFormDiffusion;
 }
 
@@ -126,9 +135,8 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 // plane's z+ face: the same two diffusivities, and the products of two FP32
 // values are exact, so the value is the one this call would form); the z+
 // face's on exit.
-// FORM = kFormConvection leaves out the Jacobi scaling select, for an
-// operator without scaling; kFormDiffusion also the convective terms, for
-// an operator without them (op_form(op) picks): with in[f] = out[f] = 0
+// FORM other than kFormGeneral (op_form(op) picks) leaves out the scaling's
+// test and, without convection, the convective terms: with in[f] = out[f] = 0
 // each fma(cD, kf, 0) is the product cD kf rounded once, so every value is
 // bit for bit the general build's.
 template <typename T, bool CELL, int FORM = kFormGeneral>
@@ -140,7 +148,7 @@ __device__ __forceinline__ T cell_apply(const Op<T>& op, T c, const T nb[6], T k
 #pragma unroll
   for (int f = 0; f < 6; ++f) {
     if (inside & (1u << f)) {
-      constexpr bool CONV = FORM != kFormDiffusion;
+      constexpr bool CONV = form_conv(FORM);
       T d_out, d_in;  // D + max(F,0), D + max(-F,0)
       if (CELL) {
         const T kf = (f == 4 && carry) ? kz
@@ -161,12 +169,13 @@ __device__ __forceinline__ T cell_apply(const Op<T>& op, T c, const T nb[6], T k
       diag += d_out;
       acc = fma_t(d_in, nb[f], acc);
     } else if (op.dir & (1u << f)) {
-      if (FORM != kFormDiffusion) diag += CELL ? fma_t(op.cD, kP, op.out[f]) : op.cD + op.out[f];
+      if (form_conv(FORM)) diag += CELL ? fma_t(op.cD, kP, op.out[f]) : op.cD + op.out[f];
       else diag += CELL ? op.cD * kP : op.cD;
     }
   }
   dg = diag;
   const T y = fma_t(diag, c, -acc);
+  if (form_scaled(FORM)) return y * pos_rcp(diag);
   if (FORM != kFormGeneral) return y;
   return op.jac ? y * pos_rcp(diag) : y;
 }
@@ -187,7 +196,7 @@ template <typename T, bool CELL, int FORM, bool XIN, bool CARRY>
 __device__ __forceinline__ T cell_apply_inner(const Op<T>& op, T c, const T nb[6], T kP,
                                               const T kN[6], bool ix0, bool ix1, T& dg, T& kz) {
 #pragma clang fp contract(off)
-  constexpr bool CONV = FORM != kFormDiffusion;
+  constexpr bool CONV = form_conv(FORM);
   T diag = T(1), acc = T(0);
 #pragma unroll
   for (int f = 0; f < 6; ++f) {
@@ -224,6 +233,7 @@ __device__ __forceinline__ T cell_apply_inner(const Op<T>& op, T c, const T nb[6
   }
   dg = diag;
   const T y = fma_t(diag, c, -acc);
+  if (form_scaled(FORM)) return y * pos_rcp(diag);
   if (FORM != kFormGeneral) return y;
   return op.jac ? y * pos_rcp(diag) : y;
 }
@@ -818,7 +828,7 @@ __device__ __forceinline__ void march_tile_lanes(const Geo& g, const Op<T>& op,
 // cell their occupancy (Ph::kWaveTests; us per pass, by lanes -> by waves):
 //   PhAC   128^3 FP64 52 -> 46, 256^3 FP64 264 -> 251, per cell 262 -> 259;
 //          FP32 128^3 per cell 38 -> 32, 512x512x256 544 -> 496; per cell with
-//          convection or scaling 142 VGPRs and 3 waves per SIMD, or 4 and
+//          convection 142 VGPRs and 3 waves per SIMD, or 4 and
 //          60 B of scratch: 192^3 74 -> 90: lanes
 //   PhA    FP32 256^3 per cell 145 -> 102   (FP64 per cell 180 -> 189: lanes)
 //   PhCg1  FP64 128^3 per cell 64 -> 43     (FP32 256^3 151 -> 157: lanes)

@@ -28,29 +28,6 @@ namespace wfa {
 // ============================================================================
 // generic stencil-pass kernel
 // ============================================================================
-// Waves per SIMD a build is compiled for (1: the compiler's choice).  At two
-// rows per wave and a diffusivity per cell: the FP64 second pass with a hashed
-// shadow fits 5 waves without spilling, in 93 VGPRs (98 and 4 waves otherwise;
-// measured 3-4% faster on 256^3), and so does the FP32 fused update pass with
-// convection, in 96; without, where it tests by waves, it fits 4 in 128 (130
-// and 3 otherwise).
-template <typename T, bool CELL, int RY, class Ph, int FORM>
-struct MinWaves {
-  static constexpr int value = 1;
-};
-template <int FORM>
-struct MinWaves<double, true, 2, PhB2<double, true>, FORM> {
-  static constexpr int value = 5;
-};
-template <int FORM>
-struct MinWaves<float, true, 2, PhAC<float, true>, FORM> {
-  static constexpr int value = FORM == kFormDiffusion ? 4 : 5;
-};
-template <>
-struct MinWaves<float, true, 2, PhAC<float, false>, kFormDiffusion> {
-  static constexpr int value = 4;
-};
-
 template <typename T, bool CELL, int RY, class Ph, class Fin, int FORM = kFormGeneral>
 __global__ void __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(MinWaves<T, CELL, RY, Ph, FORM>::value)))
@@ -76,39 +53,62 @@ k_march(Geo g, Op<T> op, const float* __restrict__ kappa, Ph ph, double* partial
   if (publish) publish_and_finalize<Ph::NV>(acc, tile, g.ntiles, partials, sc, red, fin);
 }
 
-// FORMS: the phase also has the builds of the cell operator without the
-// Jacobi scaling select and without the convective terms, launched for an
-// operator that has neither (op_form): the same values with fewer vector
-// instructions.  Only the two-reduction BiCGStab's passes on a per-cell
-// diffusivity carry them, to keep the number of kernels down.
-// FORMS_ONLY: only those two builds exist (the general ones are not
-// instantiated); the caller launches it for an operator that has one of
-// them, on a per-cell diffusivity.
-template <typename T, class Ph, class Fin, bool FORMS = false, bool FORMS_ONLY = false>
+// The cell operator's builds a phase has besides the general one (the same
+// values with fewer vector instructions), to keep the number of kernels down:
+// none; those of an operator without scaling on a per-cell diffusivity; or
+// also every operator's (op_form) at two rows per wave.  Where the update pass
+// streams a constant diffusivity or the scaled operator they measure the same
+// (192^3 FP32 70 and 69 us, scaled per cell 74 and 74), in the second pass
+// less (256^3 FP32 67 -> 60 us with the hashed shadow's build).
+enum Forms : int { kFormsNone, kFormsCell, kFormsAll };
+
+// A phase with these builds has one for the operator and its tiling.
+template <typename T>
+bool has_form(const Launch<T>& L, Forms forms) {
+  return (forms >= kFormsCell && L.cell && !L.op.jac) || (forms == kFormsAll && L.tl.ry == 2);
+}
+
+// FORMS_ONLY: only the forms' builds exist (the general ones are not
+// instantiated); the caller launches it where has_form.
+template <typename T, class Ph, class Fin, Forms FORMS = kFormsNone,
+          bool FORMS_ONLY = false>
 void dispatch_march(const Launch<T>& L, const Ph& ph, const Fin& fin, bool gated, bool publish,
                     const Scalars* after = nullptr) {
-  static_assert(FORMS || !FORMS_ONLY, "FORMS_ONLY needs FORMS");
+  static_assert(FORMS != kFormsNone || !FORMS_ONLY, "FORMS_ONLY needs FORMS");
   const Geo g = L.tl.geo;
   dim3 grid(g.ntiles), block(kThreads);
   const int G = after ? 2 : gated ? 1 : 0, P = publish ? 1 : 0;
   const Scalars* gate = after ? after : L.sc;
-#define WFA_MARCH_F(RYV, FORMV)                                                               \
-  hipLaunchKernelGGL((k_march<T, true, RYV, Ph, Fin, FORMV>), grid, block, 0, L.stream, g,     \
+#define WFA_MARCH_F(CELLV, RYV, FORMV)                                                        \
+  hipLaunchKernelGGL((k_march<T, CELLV, RYV, Ph, Fin, FORMV>), grid, block, 0, L.stream, g,    \
                      L.op, L.kappa, ph, L.partials, L.sc, fin, gate, G, P)
 #define WFA_MARCH_FORM(FORMV)                      \
   switch (L.tl.ry) {                               \
-    case 1: WFA_MARCH_F(1, FORMV); break;          \
-    case 4: WFA_MARCH_F(4, FORMV); break;          \
-    default: WFA_MARCH_F(2, FORMV); break;         \
+    case 1: WFA_MARCH_F(true, 1, FORMV); break;       \
+    case 4: WFA_MARCH_F(true, 4, FORMV); break;       \
+    default: WFA_MARCH_F(true, 2, FORMV); break;      \
   }
-  if constexpr (FORMS) {
-    if (L.cell && op_form(L.op) == kFormDiffusion) {
+  const int form = op_form(L.op);
+  if constexpr (FORMS != kFormsNone) {
+    if (L.cell && form == kFormDiffusion) {
       WFA_MARCH_FORM(kFormDiffusion);
       return;
     }
-    if (L.cell && op_form(L.op) == kFormConvection) {
+    if (L.cell && form == kFormConvection) {
       WFA_MARCH_FORM(kFormConvection);
       return;
+    }
+  }
+  if constexpr (FORMS == kFormsAll) {
+    if (has_form(L, FORMS)) {
+      switch (2 * form + (L.cell ? 1 : 0)) {
+        case 2 * kFormDiffusion: WFA_MARCH_F(false, 2, kFormDiffusion); return;
+        case 2 * kFormConvection: WFA_MARCH_F(false, 2, kFormConvection); return;
+        case 2 * kFormDiffusionScaled: WFA_MARCH_F(false, 2, kFormDiffusionScaled); return;
+        case 2 * kFormConvectionScaled: WFA_MARCH_F(false, 2, kFormConvectionScaled); return;
+        case 2 * kFormDiffusionScaled + 1: WFA_MARCH_F(true, 2, kFormDiffusionScaled); return;
+        case 2 * kFormConvectionScaled + 1: WFA_MARCH_F(true, 2, kFormConvectionScaled); return;
+      }
     }
   }
 #undef WFA_MARCH_FORM
@@ -122,13 +122,13 @@ void dispatch_march(const Launch<T>& L, const Ph& ph, const Fin& fin, bool gated
     switch (L.tl.ry) {
       case 1: WFA_MARCH(true, 1); break;
       case 4: WFA_MARCH(true, 4); break;
-      default: WFA_MARCH(true, 2); break;
+      default: if constexpr (FORMS != kFormsAll) WFA_MARCH(true, 2); break;
     }
   } else {
     switch (L.tl.ry) {
       case 1: WFA_MARCH(false, 1); break;
       case 4: WFA_MARCH(false, 4); break;
-      default: WFA_MARCH(false, 2); break;
+      default: if constexpr (FORMS != kFormsAll) WFA_MARCH(false, 2); break;
     }
   }
 #undef WFA_MARCH
@@ -194,34 +194,34 @@ void launch_phase_b(const Launch<T>& L, const T* r, const T* v, T* t) {
 template <typename T>
 void launch_phase_ac(const Launch<T>& L, const T* r, const T* v, const T* t, const T* p,
                      const T* rh, T* x, T* r_out, T* p_out, T* v_out) {
-  if (L.shadow && L.cell && op_form(L.op) != kFormGeneral) {
+  if (L.shadow && has_form(L, kFormsCell)) {
     PhAC<T, true> ph{};
     ph.hashed = 1;
     ph.r = r; ph.v = v; ph.t = t; ph.p = p; ph.rh = rh; ph.x = x;
     ph.r_out = r_out; ph.p_out = p_out; ph.v_out = v_out;
-    dispatch_march<T, PhAC<T, true>, FinAC, true, true>(L, ph, FinAC{L.sc}, true, true);
+    dispatch_march<T, PhAC<T, true>, FinAC, kFormsCell, true>(L, ph, FinAC{L.sc}, true, true);
     return;
   }
   PhAC<T> ph{};
   ph.hashed = L.shadow;
   ph.r = r; ph.v = v; ph.t = t; ph.p = p; ph.rh = rh; ph.x = x;
   ph.r_out = r_out; ph.p_out = p_out; ph.v_out = v_out;
-  dispatch_march<T, PhAC<T>, FinAC, true>(L, ph, FinAC{L.sc}, true, true);
+  dispatch_march<T, PhAC<T>, FinAC, kFormsCell>(L, ph, FinAC{L.sc}, true, true);
 }
 
 template <typename T>
 void launch_phase_b2(const Launch<T>& L, const T* r, const T* v, const T* rh, T* t) {
-  if (L.shadow && L.cell && op_form(L.op) != kFormGeneral) {
+  if (L.shadow && has_form(L, kFormsAll)) {
     PhB2<T, true> ph{};
     ph.hashed = 1;
     ph.r = r; ph.v = v; ph.rh = rh; ph.t = t;
-    dispatch_march<T, PhB2<T, true>, FinB2, true, true>(L, ph, FinB2{L.sc}, true, true);
+    dispatch_march<T, PhB2<T, true>, FinB2, kFormsAll, true>(L, ph, FinB2{L.sc}, true, true);
     return;
   }
   PhB2<T> ph{};
   ph.hashed = L.shadow;
   ph.r = r; ph.v = v; ph.rh = rh; ph.t = t;
-  dispatch_march<T, PhB2<T>, FinB2, true>(L, ph, FinB2{L.sc}, true, true);
+  dispatch_march<T, PhB2<T>, FinB2, kFormsAll>(L, ph, FinB2{L.sc}, true, true);
 }
 
 template <typename T>

@@ -518,7 +518,7 @@ struct PhAC {
   static constexpr int NV = 3;
   static constexpr int PD = 2;  // measured: 4% faster than 1 at 256^3 FP64
   template <bool CELL, int FORM> static constexpr bool kWaveTests =
-      sizeof(T) == 8 || !CELL || FORM == kFormDiffusion;
+      sizeof(T) == 8 || !CELL || !form_conv(FORM);
   using St = StageP<T>;
   static __device__ __forceinline__ T val(const St& u) { return u.p; }
   static __device__ __forceinline__ T val(T u) { return u; }
@@ -961,5 +961,24 @@ __device__ __forceinline__ void cg_b_tile(const Geo& g, int tile, T* __restrict_
         st_once(r + e, c.r);
       });
 }
+
+// Waves per SIMD a build is compiled for (1: the compiler's choice).  At two
+// rows per wave and a diffusivity per cell: the FP64 second pass with a hashed
+// shadow fits 5 waves without spilling, in 93 VGPRs (98 and 4 waves otherwise;
+// measured 3-4% faster on 256^3), and so does the FP32 fused update pass with
+// convection, in 96; without, where it tests by waves, it fits 4 in 128 (130
+// to 133 and 3 otherwise).
+template <typename T, bool CELL, int RY, class Ph, int FORM>
+struct MinWaves {
+  static constexpr int value = 1;
+};
+template <int FORM>
+struct MinWaves<double, true, 2, PhB2<double, true>, FORM> {
+  static constexpr int value = 5;
+};
+template <bool HASHED, int FORM>
+struct MinWaves<float, true, 2, PhAC<float, HASHED>, FORM> {
+  static constexpr int value = !form_conv(FORM) ? 4 : HASHED ? 5 : 1;
+};
 
 }  // namespace wfa

@@ -669,12 +669,15 @@ void worker_main(wfa_server* sv, int lane) {
           e = launch_batch_persistent<double>(ln.d64, ln.bases + 2 * (S + 1), t64, n64, chunk,
                                               ln.ry, ln.bar, kRoundSpinLimit, ln.stream);
       } else {
+        const int build32 = batch_build(&ln.h_d32[0], n32, ln.ry);
+        const int build64 = batch_build(&ln.h_d64[0], n64, ln.ry);
         for (int q = 0; q < chunk; ++q) {
           if (n32)
-            launch_batch_iteration2<float>(ln.d32, ln.bases, t32, n32, q, ln.ry, ln.stream);
+            launch_batch_iteration2<float>(ln.d32, ln.bases, t32, n32, q, ln.ry, build32,
+                                           ln.stream);
           if (n64)
             launch_batch_iteration2<double>(ln.d64, ln.bases + 2 * (S + 1), t64, n64, q, ln.ry,
-                                            ln.stream);
+                                            build64, ln.stream);
         }
         e = hipGetLastError();
       }
