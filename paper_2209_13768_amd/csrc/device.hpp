@@ -134,7 +134,9 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 // kz: with `carry`, the z- face's harmonic mean on entry (the previous
 // plane's z+ face: the same two diffusivities, and the products of two FP32
 // values are exact, so the value is the one this call would form); the z+
-// face's on exit.
+// face's on exit.  ky: so for the y faces, with carry_y, of the thread's rows
+// in order (one harmonic mean less for every row but the first: 512x512x256
+// FP64 apply 329 -> 320 us, one explicit step 471 -> 449 us).
 // FORM other than kFormGeneral (op_form(op) picks) leaves out the scaling's
 // test and, without convection, the convective terms: with in[f] = out[f] = 0
 // each fma(cD, kf, 0) is the product cD kf rounded once, so every value is
@@ -142,7 +144,7 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 template <typename T, bool CELL, int FORM = kFormGeneral>
 __device__ __forceinline__ T cell_apply(const Op<T>& op, T c, const T nb[6], T kP,
                                         const T kN[6], uint32_t inside, T& dg, T& kz,
-                                        bool carry) {
+                                        bool carry, T& ky, bool carry_y) {
 #pragma clang fp contract(off)
   T diag = T(1), acc = T(0);
 #pragma unroll
@@ -151,9 +153,11 @@ __device__ __forceinline__ T cell_apply(const Op<T>& op, T c, const T nb[6], T k
       constexpr bool CONV = form_conv(FORM);
       T d_out, d_in;  // D + max(F,0), D + max(-F,0)
       if (CELL) {
-        const T kf = (f == 4 && carry) ? kz
-                                       : T(2) * kP * kN[f] * pos_rcp(kP + kN[f]);  // harmonic mean
+        const T kf = (f == 4 && carry)     ? kz
+                     : (f == 2 && carry_y) ? ky
+                                           : T(2) * kP * kN[f] * pos_rcp(kP + kN[f]);  // harmonic mean
         if (f == 5) kz = kf;
+        if (f == 3) ky = kf;
         if (CONV) {
           d_out = fma_t(op.cD, kf, op.out[f]);
           d_in = fma_t(op.cD, kf, op.in[f]);
@@ -183,18 +187,19 @@ __device__ __forceinline__ T cell_apply(const Op<T>& op, T c, const T nb[6], T k
 template <typename T, bool CELL, int FORM = kFormGeneral>
 __device__ __forceinline__ T cell_apply(const Op<T>& op, T c, const T nb[6], T kP,
                                         const T kN[6], uint32_t inside, T& dg) {
-  T kz = T(0);
-  return cell_apply<T, CELL, FORM>(op, c, nb, kP, kN, inside, dg, kz, false);
+  T kz = T(0), ky = T(0);
+  return cell_apply<T, CELL, FORM>(op, c, nb, kP, kN, inside, dg, kz, false, ky, false);
 }
 
 // cell_apply where the y and z neighbours all exist (a wave's rows and plane
 // say so for all its lanes) and, with XIN, the x neighbours too: the same
 // operations without a branch per face, so that a thread's rows and their
 // faces are in flight together.  ix0, ix1: the x neighbours exist.  CARRY: the
-// z- face's harmonic mean is kz (see cell_apply).
+// z- face's harmonic mean is kz; ky: see cell_apply.
 template <typename T, bool CELL, int FORM, bool XIN, bool CARRY>
 __device__ __forceinline__ T cell_apply_inner(const Op<T>& op, T c, const T nb[6], T kP,
-                                              const T kN[6], bool ix0, bool ix1, T& dg, T& kz) {
+                                              const T kN[6], bool ix0, bool ix1, T& dg, T& kz,
+                                              T& ky, bool carry_y) {
 #pragma clang fp contract(off)
   constexpr bool CONV = form_conv(FORM);
   T diag = T(1), acc = T(0);
@@ -202,8 +207,11 @@ __device__ __forceinline__ T cell_apply_inner(const Op<T>& op, T c, const T nb[6
   for (int f = 0; f < 6; ++f) {
     T d_out, d_in;
     if (CELL) {
-      const T kf = (f == 4 && CARRY) ? kz : T(2) * kP * kN[f] * pos_rcp(kP + kN[f]);
+      const T kf = (f == 4 && CARRY)     ? kz
+                   : (f == 2 && carry_y) ? ky
+                                         : T(2) * kP * kN[f] * pos_rcp(kP + kN[f]);
       if (f == 5) kz = kf;
+      if (f == 3) ky = kf;
       if (CONV) {
         d_out = fma_t(op.cD, kf, op.out[f]);
         d_in = fma_t(op.cD, kf, op.in[f]);
@@ -772,15 +780,19 @@ __device__ __forceinline__ void march_tile_lanes(const Geo& g, const Op<T>& op,
 
     // compute plane k
     const uint32_t ins_z = (k > 0 ? 16u : 0u) | (k < nz - 1 ? 32u : 0u);
+    T ky = T(0);
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
       if (own[r]) {
         const int l = lidx[r];
-        T nb[6] = {Lu[l - 1], Lu[l + 1], Lu[l - LW], Lu[l + LW], up[r], unv[r]};
+        T nb[6] = {Lu[l - 1], Lu[l + 1], r > 0 ? Ph::val(uc[max(r - 1, 0)]) : Lu[l - LW],
+                   r < RY - 1 ? Ph::val(uc[min(r + 1, RY - 1)]) : Lu[l + LW], up[r], unv[r]};
         T kn6[6];
         if (CELL) {
-          kn6[0] = (T)Lk[l - 1]; kn6[1] = (T)Lk[l + 1]; kn6[2] = (T)Lk[l - LW];
-          kn6[3] = (T)Lk[l + LW]; kn6[4] = (T)kpv[r]; kn6[5] = (T)knv[r];
+          kn6[0] = (T)Lk[l - 1]; kn6[1] = (T)Lk[l + 1];
+          kn6[2] = (T)(r > 0 ? kcv[max(r - 1, 0)] : Lk[l - LW]);
+          kn6[3] = (T)(r < RY - 1 ? kcv[min(r + 1, RY - 1)] : Lk[l + LW]);
+          kn6[4] = (T)kpv[r]; kn6[5] = (T)knv[r];
         } else {
 #pragma unroll
           for (int f = 0; f < 6; ++f) kn6[f] = T(1);
@@ -790,9 +802,10 @@ __device__ __forceinline__ void march_tile_lanes(const Geo& g, const Op<T>& op,
         T Au;
         if constexpr (CZ)
           Au = cell_apply<T, CELL, FORM>(op, Ph::val(uc[r]), nb, (T)kcv[r], kn6, ins, dg, kz[r],
-                                         carry);
+                                         carry, ky, r > 0);
         else
-          Au = cell_apply<T, CELL, FORM>(op, Ph::val(uc[r]), nb, (T)kcv[r], kn6, ins, dg);
+          Au = cell_apply<T, CELL, FORM>(op, Ph::val(uc[r]), nb, (T)kcv[r], kn6, ins, dg, kz[r],
+                                         false, ky, r > 0);
         ph.epilogue((size_t)k * plane + poff[r], uc[r], Au, (T)kcv[r], ins, ec[r], dg, acc);
       }
     }
@@ -1047,15 +1060,18 @@ __device__ __forceinline__ void march_tile_waves(const Geo& g, const Op<T>& op,
     // compute plane k
     T Au[RY], dg[RY];
     T nb[RY][6], kn6[RY][6];
+    T ky = T(0);
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
       const int l = lidx[r];
       nb[r][0] = Lu[l - 1]; nb[r][1] = Lu[l + 1];
-      nb[r][2] = Lu[l - LW]; nb[r][3] = Lu[l + LW];
+      nb[r][2] = r > 0 ? Ph::val(uc[max(r - 1, 0)]) : Lu[l - LW];
+      nb[r][3] = r < RY - 1 ? Ph::val(uc[min(r + 1, RY - 1)]) : Lu[l + LW];
       nb[r][4] = up[r]; nb[r][5] = unv[r];
       if (CELL) {
         kn6[r][0] = (T)Lk[l - 1]; kn6[r][1] = (T)Lk[l + 1];
-        kn6[r][2] = (T)Lk[l - LW]; kn6[r][3] = (T)Lk[l + LW];
+        kn6[r][2] = (T)(r > 0 ? kcv[max(r - 1, 0)] : Lk[l - LW]);
+        kn6[r][3] = (T)(r < RY - 1 ? kcv[min(r + 1, RY - 1)] : Lk[l + LW]);
         kn6[r][4] = (T)kpv[r]; kn6[r][5] = (T)knv[r];
       } else {
 #pragma unroll
@@ -1067,12 +1083,14 @@ __device__ __forceinline__ void march_tile_waves(const Geo& g, const Op<T>& op,
 #pragma unroll
         for (int r = 0; r < RY; ++r)
           Au[r] = cell_apply_inner<T, CELL, FORM, true, CZ>(op, Ph::val(uc[r]), nb[r], (T)kcv[r],
-                                                            kn6[r], true, true, dg[r], kz[r]);
+                                                            kn6[r], true, true, dg[r], kz[r],
+                                                            ky, r > 0);
       } else {
 #pragma unroll
         for (int r = 0; r < RY; ++r)
           Au[r] = cell_apply_inner<T, CELL, FORM, false, CZ>(op, Ph::val(uc[r]), nb[r], (T)kcv[r],
-                                                             kn6[r], ix0, ix1, dg[r], kz[r]);
+                                                             kn6[r], ix0, ix1, dg[r], kz[r], ky,
+                                                             r > 0);
       }
     } else {
       const uint32_t ins_z = (k > 0 ? 16u : 0u) | (k < nz - 1 ? 32u : 0u);
@@ -1080,10 +1098,10 @@ __device__ __forceinline__ void march_tile_waves(const Geo& g, const Op<T>& op,
       for (int r = 0; r < RY; ++r) {
         if constexpr (CZ)
           Au[r] = cell_apply<T, CELL, FORM>(op, Ph::val(uc[r]), nb[r], (T)kcv[r], kn6[r],
-                                            ins_xy[r] | ins_z, dg[r], kz[r], true);
+                                            ins_xy[r] | ins_z, dg[r], kz[r], true, ky, r > 0);
         else
           Au[r] = cell_apply<T, CELL, FORM>(op, Ph::val(uc[r]), nb[r], (T)kcv[r], kn6[r],
-                                            ins_xy[r] | ins_z, dg[r]);
+                                            ins_xy[r] | ins_z, dg[r], kz[r], false, ky, r > 0);
       }
     }
     const uint32_t ins_z = (k > 0 ? 16u : 0u) | (k < nz - 1 ? 32u : 0u);
