@@ -566,8 +566,8 @@ __device__ __forceinline__ void store_partial(double* region, int nslots, int sl
 // the 4 waves owns RY consecutive rows; lane l owns column x0 + l.  For each
 // output plane k the staged vector u (computed on the fly from the phase's
 // input arrays, also on the x-y halo) is written to an LDS plane with a
-// one-cell halo; the x and y neighbours come from LDS and the z neighbours
-// from registers (u at k-1 and k+1).  Loads for plane k+2 and the
+// one-cell halo; the x and y neighbours come from LDS (a thread's own rows
+// from registers) and the z neighbours from registers (u at k-1 and k+1).  Loads for plane k+2 and the
 // epilogue's loads for plane k+1 are issued before plane k is computed, so
 // one plane of work hides each load's latency.
 //

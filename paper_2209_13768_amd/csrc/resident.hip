@@ -76,7 +76,9 @@ struct Empty<float> {
   static constexpr Bits value = 0x7fc5eed1u, nan = 0x7fc00000u;
 };
 constexpr int kRing = 3;
-constexpr int kSpinLimit = 1 << 20;   // polls of one wait (each a trip to memory)
+// Polls of one wait, each a trip to memory of 0.5 us or more: seconds, for a
+// workgroup that other streams' kernels keep from its CU.
+constexpr int kSpinLimit = 1 << 23;
 
 template <typename T>
 struct ResArgs {
