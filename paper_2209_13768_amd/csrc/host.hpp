@@ -62,7 +62,7 @@ struct GraphCache {
 // polls (a wait of a few tens of microseconds is common on small grids, and
 // polling answers sooner than a blocking wait).
 struct Readback {
-  static constexpr int kSlots = 2;
+  static constexpr int kSlots = 3;   // a grid's scalar blocks (solve, inner, residual)
   Scalars* host = nullptr;   // kSlots blocks (hipHostMalloc), or `local` in sync mode
   hipEvent_t done = nullptr;
   // sync mode: the copies land in `local` (pageable host memory) and the

@@ -151,9 +151,10 @@ bool resident_fits(const Launch<T>& L, int kind);
 template <typename T>
 hipError_t launch_resident(const Launch<T>& L, int kind, const ResidentVectors<T>& v, int iters,
                            int parity);
-// launch_set_scalars, and the ring of a grid of `ntiles` tiles emptied
+// launch_set_scalars, with v2 *dst2 = *v2 in the same launch, and the ring of a
+// grid of `ntiles` tiles emptied
 void launch_set_resident(Scalars* dst, const Scalars& v, double* ring, int copies, int ntiles,
-                         hipStream_t s);
+                         hipStream_t s, Scalars* dst2, const Scalars* v2);
 
 // Streams a probe kind reads and writes: `bytes` each (a copy: 2; a stream
 // mix: its reads and writes).

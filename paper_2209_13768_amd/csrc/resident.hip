@@ -1013,15 +1013,17 @@ hipError_t launch_resident(const Launch<T>& L, int kind, const ResidentVectors<T
 
 // The solve's scalars, with every slot of the ring empty.
 __global__ void __launch_bounds__(1024)
-k_set_resident(Scalars* __restrict__ dst, Scalars v, uint64_t* __restrict__ ring, int slots) {
+k_set_resident(Scalars* __restrict__ dst, Scalars v, Scalars* __restrict__ dst2, Scalars v2,
+               uint64_t* __restrict__ ring, int slots) {
   if (threadIdx.x == 0) *dst = v;
+  if (threadIdx.x == 1 && dst2) *dst2 = v2;
   for (int e = threadIdx.x; e < slots; e += 1024) ring[e] = Empty<double>::value;
 }
 
 void launch_set_resident(Scalars* dst, const Scalars& v, double* ring, int copies, int ntiles,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(k_set_resident, dim3(1), dim3(1024), 0, s, dst, v, (uint64_t*)ring,
-                     copies * kRing * kMaxReduce * ntiles);
+                         hipStream_t s, Scalars* dst2, const Scalars* v2) {
+  hipLaunchKernelGGL(k_set_resident, dim3(1), dim3(1024), 0, s, dst, v, v2 ? dst2 : nullptr,
+                     v2 ? *v2 : v, (uint64_t*)ring, copies * kRing * kMaxReduce * ntiles);
 }
 
 // Copies of the ring that fit in `doubles` (a power of two, one per XCD at most).
