@@ -246,7 +246,12 @@ enum {
                                   registers, one cooperative launch per chunk
                                   of iterations (bitwise the same results; not
                                   with WFA_OPT_PROFILE, _GRAPH or
-                                  _RECOMPUTE_T),
+                                  _RECOMPUTE_T).  Such a launch needs all its
+                                  workgroups on the GPU at once.  Where other
+                                  streams' or processes' kernels keep one off
+                                  for some 0.1 s it gives up; that solve and
+                                  the grid's next 255 then go on with one
+                                  launch per pass (wfa_resident_stats);
                                   1: one persistent launch per solve chunk,
                                   -1: automatic by grid size                   */
   WFA_OPT_PROFILE = 3,         /* n > 0: time every n-th launch of each
@@ -318,9 +323,15 @@ enum {
                                   (default)                                    */
   WFA_OPT_SIZE_CLASS_1 = 16,   /* server only: upper bounds (cells) of the   */
   WFA_OPT_SIZE_CLASS_2 = 17,   /* size classes, each served by its own host  */
-  WFA_OPT_SIZE_CLASS_3 = 18    /* thread and HIP stream; 0 = no further class
+  WFA_OPT_SIZE_CLASS_3 = 18,   /* thread and HIP stream; 0 = no further class
                                   (defaults 884736, 3511808, 0: three classes,
                                   up to 96^3, 152^3 and above)                */
+  WFA_OPT_FORCE_GIVE_UP = 19   /* n > 0: one workgroup is missing from the
+                                  grid's n-th launch of resident iterations
+                                  from now (WFA_OPT_PERSISTENT 0), as if
+                                  another kernel held its CU, so that the
+                                  launch gives up (once), to exercise the
+                                  recovery from the host                      */
 };
 int wfa_grid_set_option(wfa_grid* g, int option, int64_t value);
 
@@ -336,6 +347,11 @@ enum {
  * (the streams the kernel must read and write once).  reset != 0 clears. */
 int wfa_kernel_stats(wfa_grid* g, int kernel, int64_t* launches, double* ms,
                      double* bytes_per_launch, int reset);
+
+/* Launches of resident iterations (WFA_OPT_PERSISTENT 0) the grid's solves
+ * have made since it was created or since the last reset, and how many of
+ * them gave up.  Either pointer may be NULL; reset != 0 clears both. */
+int wfa_resident_stats(wfa_grid* g, int64_t* launches, int64_t* gave_up, int reset);
 
 /* Tile shape the grid uses: x cells, y cells, z planes per workgroup, and
  * the number of workgroups of one phase launch. */

@@ -181,6 +181,9 @@ void grid_setup(wfa_grid* g, int nx, int ny, int nz, const wfa_coeffs* c, char* 
   g->check_every = 0;
   g->ir_inner_tol = 1e-4;
   g->force_div = 0;
+  g->absent = 0;
+  g->resident_launches = g->resident_gave_up = 0;
+  g->per_pass_solves = 0;
   g->hint_iters = 0;
   g->jacobi = 0;
   g->graph = 0;
@@ -252,6 +255,10 @@ extern "C" int wfa_grid_set_option(wfa_grid* g, int option, int64_t value) {
     case WFA_OPT_FORCE_DIVERGE:
       if (value < 0) return set_error(WFA_ERR_INVALID, "bad divergence iteration");
       g->force_div = (int)value;
+      return WFA_OK;
+    case WFA_OPT_FORCE_GIVE_UP:
+      if (value < 0 || value > (1 << 20)) return set_error(WFA_ERR_INVALID, "bad launch number");
+      g->absent = (int)value;
       return WFA_OK;
     case WFA_OPT_IR_INNER_TOL:
       if (value <= 0) return set_error(WFA_ERR_INVALID, "bad inner tolerance");
@@ -434,6 +441,14 @@ extern "C" int wfa_kernel_stats(wfa_grid* g, int kernel, int64_t* launches, doub
 // ---------------------------------------------------------------------------
 // launch contexts
 // ---------------------------------------------------------------------------
+extern "C" int wfa_resident_stats(wfa_grid* g, int64_t* launches, int64_t* gave_up, int reset) {
+  if (!g) return set_error(WFA_ERR_INVALID, "grid is NULL");
+  if (launches) *launches = g->resident_launches;
+  if (gave_up) *gave_up = g->resident_gave_up;
+  if (reset) g->resident_launches = g->resident_gave_up = 0;
+  return WFA_OK;
+}
+
 template <typename T>
 static Launch<T> ctx(wfa_grid* g, Scalars* sc, hipStream_t s);
 
@@ -594,7 +609,7 @@ static int write_scalars(const Scalars* host, Scalars* dev, hipStream_t s) {
 template <typename T>
 static int write_solve_scalars(const Launch<T>& L, const Scalars* host, const Scalars* host2,
                                Scalars* dev2) {
-  if (L.tl.geo.ntiles > kResidentTiles) {
+  if (L.tl.geo.ntiles > kResidentTiles || !L.ring) {
     if (host2) launch_set_scalars(dev2, *host2, L.stream);
     return write_scalars(host, L.sc, L.stream);
   }
@@ -765,6 +780,7 @@ static void graph_key(uint64_t (&k)[GraphCache::kKey], const wfa_grid* g, const 
 // a queue).
 template <typename T>
 static bool use_resident(const wfa_grid* g, const Launch<T>& L, int kind) {
+  if (g->per_pass_solves > 0) return false;
   if (g->profile || g->persistent != 0 || g->recompute_t || g->rb.sync || use_graph(g)) return false;
   return resident_fits<T>(L, kind);
 }
@@ -774,6 +790,38 @@ static bool use_resident(const wfa_grid* g, const Launch<T>& L, int kind) {
 static int resident_chunk(const wfa_grid* g, int budget) {
   const int m = g->check_every > 0 ? g->check_every : 512;
   return m < budget ? m : budget < 1 ? 1 : budget;
+}
+
+// A resident launch gave up: its workgroups were not all on a CU within the
+// bound of their waits (0.07 s each), because another stream's or process's
+// kernels held some.  What the iterations had in the workspace is lost; x is
+// as it was when the launch started, or holds a newer iterate in some tiles.
+// The solve goes on from x with one launch per pass, and so do the grid's next
+// solves: whoever holds the CUs may do so for longer, and giving up costs as
+// much as some hundred small solves.
+constexpr int kGaveUp = 1;
+constexpr int kPerPassSolves = 256;
+
+template <typename T>
+static void resident_gave_up(wfa_grid* g, Launch<T>& L) {
+  ++g->resident_gave_up;
+  g->per_pass_solves = kPerPassSolves;
+  L.ring = nullptr;
+}
+
+// `iters` resident iterations; false where the runtime refuses the launch,
+// which then has done nothing.
+template <typename T>
+static bool resident_iterations(wfa_grid* g, const Launch<T>& L, int kind,
+                                const ResidentVectors<T>& vec, int iters, int par) {
+  const bool absent = g->absent == 1 && L.tl.geo.ntiles > 1;
+  if (launch_resident<T>(L, kind, vec, iters, par, absent) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (g->absent > 0) --g->absent;
+  ++g->resident_launches;
+  return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -790,6 +838,8 @@ static int resident_chunk(const wfa_grid* g, int budget) {
 // instruction).  The same holds after a restart.
 // Each chunk's scalars are read back once, together with the optional
 // `tail`: a second scalar block, and a pass queued behind every chunk.
+// The loops return kGaveUp, with the iterations before that chunk in h, when
+// a resident launch gave up; the caller starts the solve again from x.
 
 // Queued behind every chunk of iterations and read back with it.
 struct ChunkTail {
@@ -805,10 +855,12 @@ static int read_chunk(wfa_grid* g, const Scalars* dev, Scalars* h, hipStream_t s
     int rc = check_launch("tail");
     if (rc) return rc;
   }
+  const int iter = h->iter;
   const int rc = read_scalars(g, dev, h, s, tail ? tail->dev : nullptr, tail ? tail->host : nullptr);
   if (rc) return rc;
-  if (h->timeout) return set_error(WFA_ERR_HIP, "resident iterations: an exchange timed out");
-  return WFA_OK;
+  if (!h->timeout) return WFA_OK;
+  h->iter = iter;
+  return kGaveUp;
 }
 
 template <typename T>
@@ -817,7 +869,7 @@ static int iterate_bicgstab(wfa_grid* g, const Launch<T>& L, T* x, T* r, T* spar
                             ChunkTail* tail, int hint) {
   int par = 0;
   int rc = WFA_OK;
-  const bool resident = use_resident(g, L, kResidentBicgstab);
+  bool resident = use_resident(g, L, kResidentBicgstab);
   if (use_persistent(g, L.tl)) {
     if ((rc = reset_barrier(g, L.stream))) return rc;
     if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
@@ -838,9 +890,10 @@ static int iterate_bicgstab(wfa_grid* g, const Launch<T>& L, T* x, T* r, T* spar
     if (resident) {
       const int m = resident_chunk(g, h->maxit - h->iter);
       const ResidentVectors<T> vec{x, rh, t, {r, spare}, {p[0], p[1]}, {v[0], v[1]}};
-      const hipError_t e = launch_resident<T>(L, kResidentBicgstab, vec, m, par);
-      if (e != hipSuccess)
-        return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
+      if (!resident_iterations(g, L, kResidentBicgstab, vec, m, par)) {
+        resident = false;
+        continue;
+      }
       par ^= m & 1;
       if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
       continue;
@@ -908,7 +961,7 @@ static int iterate_bicgstab2(wfa_grid* g, const Launch<T>& L, T* x, T** r, T* rh
   // With recompute_t pass 1 forms t = A s again and pass 2 stores nothing:
   // bitwise the same iterates, two vector streams fewer per iteration.
   const bool recompute = g->recompute_t != 0;
-  const bool resident = use_resident(g, L, kResidentBicgstab2);
+  bool resident = use_resident(g, L, kResidentBicgstab2);
   auto pass_pair = [&](const Launch<T>& Lp, int pp) {
     {
       ProfScope ps(g, WFA_K_PHASE_AC, Lp.stream);
@@ -937,9 +990,10 @@ static int iterate_bicgstab2(wfa_grid* g, const Launch<T>& L, T* x, T** r, T* rh
     if (resident) {
       const int m = resident_chunk(g, h->maxit - h->iter + 1);
       const ResidentVectors<T> vec{x, rh, t, {r[0], r[1]}, {p[0], p[1]}, {v[0], v[1]}};
-      const hipError_t e = launch_resident<T>(L, kResidentBicgstab2, vec, m, par);
-      if (e != hipSuccess)
-        return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
+      if (!resident_iterations(g, L, kResidentBicgstab2, vec, m, par)) {
+        resident = false;
+        continue;
+      }
       par ^= m & 1;
       if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
       continue;
@@ -975,14 +1029,15 @@ static int iterate_cg(wfa_grid* g, const Launch<T>& L, T* x, T* r, T** d, T* q, 
                       Scalars* h, ChunkTail* tail, int hint) {
   int par = 0;
   int rc = WFA_OK;
-  const bool resident = use_resident(g, L, kResidentCg);
+  bool resident = use_resident(g, L, kResidentCg);
   while (h->status == ST_RUN) {
     if (resident) {
       const int m = resident_chunk(g, h->maxit - h->iter);
       const ResidentVectors<T> vec{x, nullptr, q, {r, nullptr}, {d[0], d[1]}, {spare[0], spare[1]}};
-      const hipError_t e = launch_resident<T>(L, kResidentCg, vec, m, par);
-      if (e != hipSuccess)
-        return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
+      if (!resident_iterations(g, L, kResidentCg, vec, m, par)) {
+        resident = false;
+        continue;
+      }
       par ^= m & 1;
       if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
       continue;
@@ -1030,14 +1085,15 @@ static int iterate_cg1(wfa_grid* g, const Launch<T>& L, T* x, T** r, T** w, T** 
                        Scalars* h, ChunkTail* tail, int hint) {
   int par = 0;
   int rc = WFA_OK;
-  const bool resident = use_resident(g, L, kResidentCg1);
+  bool resident = use_resident(g, L, kResidentCg1);
   while (h->status == ST_RUN) {
     if (resident) {
       const int m = resident_chunk(g, h->maxit - h->iter + (h->stage == 0 ? 1 : 0));
       const ResidentVectors<T> vec{x, nullptr, p, {r[0], r[1]}, {sv[0], sv[1]}, {w[0], w[1]}};
-      const hipError_t e = launch_resident<T>(L, kResidentCg1, vec, m, par);
-      if (e != hipSuccess)
-        return set_error(WFA_ERR_HIP, "resident launch: %s", hipGetErrorString(e));
+      if (!resident_iterations(g, L, kResidentCg1, vec, m, par)) {
+        resident = false;
+        continue;
+      }
       par ^= m & 1;
       if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
       continue;
@@ -1143,16 +1199,26 @@ static int solve_plain(wfa_grid* g, const T* b_user, T* x, bool form_b, double t
   int rpar = 0;
   ChunkTail* tp = use_tail ? &tail : nullptr;
   const int hint = g->hint_iters;
-  if (g->method == WFA_METHOD_CG) {
-    rc = iterate_cg<T>(g, L, x, r, p, t, v, &h, tp, hint);
-  } else if (g->method == WFA_METHOD_CG1) {
-    T* w[2] = {v[0], v[1]};
-    rc = iterate_cg1<T>(g, L, x, rbuf, w, p, t, &h, tp, hint);
+  for (;;) {
+    if (g->method == WFA_METHOD_CG) {
+      rc = iterate_cg<T>(g, L, x, r, p, t, v, &h, tp, hint);
+    } else if (g->method == WFA_METHOD_CG1) {
+      T* w[2] = {v[0], v[1]};
+      rc = iterate_cg1<T>(g, L, x, rbuf, w, p, t, &h, tp, hint);
+    } else if (g->method == WFA_METHOD_BICGSTAB2) {
+      rc = iterate_bicgstab2<T>(g, L, x, rbuf, rh, p, v, t, b, &h, &restarts, &rpar, true, tp, hint);
+    } else {
+      rc = iterate_bicgstab<T>(g, L, x, r, vec[8], rh, p, v, t, b, &h, &restarts, true, tp, hint);
+    }
+    if (rc != kGaveUp) break;
+    resident_gave_up(g, L);
+    h.status = ST_RUN;
+    h.restart = h.timeout = h.counter = 0;
+    ha = fresh_scalars(1.0, 1, 0);
+    if ((rc = write_solve_scalars(L, &h, use_tail ? &ha : nullptr, g->sc_aux))) return rc;
+    launch_init<T>(L, false, x, b, nullptr, r, rh);
+    if ((rc = check_launch("init"))) return rc;
   }
-  else if (g->method == WFA_METHOD_BICGSTAB2)
-    rc = iterate_bicgstab2<T>(g, L, x, rbuf, rh, p, v, t, b, &h, &restarts, &rpar, true, tp, hint);
-  else
-    rc = iterate_bicgstab<T>(g, L, x, r, vec[8], rh, p, v, t, b, &h, &restarts, true, tp, hint);
   if (rc) return rc;
   g->hint_iters = h.status == ST_CONV && restarts == 0 ? h.iter : 0;
   int status;
@@ -1276,6 +1342,11 @@ static int solve_ir(wfa_grid* g, const double* b_user, double* x, bool form_b, d
       else
         rc = iterate_bicgstab2<float>(g, L32, d, rbuf, rh, p, v, t, nullptr, &hi,
                                       &inner_restarts, &inner_par, false, &outer, g->hint_iters);
+      if (rc == kGaveUp) {   // this refinement again
+        resident_gave_up(g, L32);
+        --ref;
+        continue;
+      }
       if (rc) return rc;
       g->hint_iters = hi.status == ST_CONV && !hi.restart && hi.iter > 0 ? hi.iter : 0;
     }
@@ -1358,6 +1429,7 @@ int solve_any(wfa_grid* g, const void* b, void* x, bool form_b, double tol, int 
   if (g->jacobi && (cg || g->prec == WFA_F32_IR64))
     return set_error(WFA_ERR_INVALID,
                      "Jacobi scaling is available for BiCGStab on WFA_F64 / WFA_F32 grids");
+  if (g->per_pass_solves > 0) --g->per_pass_solves;
   switch (g->prec) {
     case WFA_F64: return solve_plain<double>(g, (const double*)b, (double*)x, form_b, tol, maxit, info, s);
     case WFA_F32: return solve_plain<float>(g, (const float*)b, (float*)x, form_b, tol, maxit, info, s);

@@ -109,6 +109,9 @@ struct wfa_grid {
   int recompute_t;  // two-reduction BiCGStab: pass 1 forms t = A s again (not stored)
   double ir_inner_tol;
   int force_div;         // n > 0: the next IR solve's first inner solve diverges at n
+  int absent;            // n > 0: a tile is missing from the n-th resident launch from now
+  int64_t resident_launches, resident_gave_up;   // see wfa_resident_stats
+  int per_pass_solves;   // solves still to make with one launch per pass, after a give-up
   int hint_iters;        // iterations of the last converged (inner) solve: first chunk size
   wfa::Profiler prof;
   wfa::GraphCache graphs;

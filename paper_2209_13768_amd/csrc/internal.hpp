@@ -41,7 +41,7 @@ struct Launch {
   double* partials;
   Scalars* sc;
   hipStream_t stream;
-  double* ring;   // exchange slots of the resident iterations
+  double* ring;   // exchange slots of the resident iterations (null: not to iterate resident)
   int ring_copies;
   int shadow;   // 1: the two-reduction BiCGStab's shadow residual is index-hashed
 };
@@ -148,9 +148,11 @@ struct ResidentVectors {
 int ring_copies(size_t doubles, int ntiles);
 template <typename T>
 bool resident_fits(const Launch<T>& L, int kind);
+// absent: the launch lacks the last tile's workgroup, as if another kernel held
+// its CU (a test hook, for grids of two tiles or more).
 template <typename T>
 hipError_t launch_resident(const Launch<T>& L, int kind, const ResidentVectors<T>& v, int iters,
-                           int parity);
+                           int parity, bool absent);
 // launch_set_scalars, with v2 *dst2 = *v2 in the same launch, and the ring of a
 // grid of `ntiles` tiles emptied
 void launch_set_resident(Scalars* dst, const Scalars& v, double* ring, int copies, int ntiles,

@@ -26,6 +26,7 @@ OPT_IR_INNER_TOL, OPT_ZCHUNK, OPT_RY, OPT_JACOBI, OPT_GRAPH = 6, 7, 8, 9, 10
 OPT_EXPLICIT_FUSE, OPT_SHADOW, OPT_FORCE_DIVERGE, OPT_CG1_MAX_CELLS = 11, 12, 13, 14
 OPT_RECOMPUTE_T = 15
 OPT_SIZE_CLASS_1, OPT_SIZE_CLASS_2, OPT_SIZE_CLASS_3 = 16, 17, 18
+OPT_FORCE_GIVE_UP = 19
 K_APPLY, K_INIT, K_PHASE_A, K_PHASE_B, K_PHASE_C, K_RESIDUAL, K_PROMOTE = 0, 1, 2, 3, 4, 5, 6
 K_CG_A, K_CG_B, K_PERSISTENT, K_PHASE_AC, K_PHASE_B2, K_EXPLICIT = 7, 8, 9, 10, 11, 12
 K_EXPLICIT_FUSED, K_CG1, K_COUNT = 13, 14, 15
@@ -46,7 +47,7 @@ PRECISIONS = {"f64": F64, "f32": F32, "f32_ir64": F32_IR64}
 EXPORTS = (
     "wfa_workspace_bytes", "wfa_grid_create", "wfa_grid_destroy", "wfa_stencil_apply",
     "wfa_rhs", "wfa_explicit_step", "wfa_bicgstab_solve", "wfa_bicgstab2_solve", "wfa_cg_solve", "wfa_cg1_solve", "wfa_timestep", "wfa_true_residual",
-    "wfa_grid_set_option", "wfa_kernel_stats", "wfa_grid_tiling", "wfa_grid_vector",
+    "wfa_grid_set_option", "wfa_kernel_stats", "wfa_resident_stats", "wfa_grid_tiling", "wfa_grid_vector",
     "wfa_stream_probe", "wfa_bandwidth_probe", "wfa_bicgstab_solve_static",
     "wfa_server_create", "wfa_server_set_option", "wfa_submit", "wfa_poll", "wfa_server_drain",
     "wfa_server_destroy",
@@ -136,6 +137,7 @@ def lib() -> ctypes.CDLL:
     L.wfa_grid_set_option.argtypes = [vp, i32, i64]
     L.wfa_kernel_stats.argtypes = [vp, i32, ctypes.POINTER(i64), ctypes.POINTER(dbl),
                                    ctypes.POINTER(dbl), i32]
+    L.wfa_resident_stats.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(i64), i32]
     L.wfa_grid_tiling.argtypes = [vp] + [ctypes.POINTER(i32)] * 4
     L.wfa_grid_vector.argtypes = [vp, i32, ctypes.POINTER(vp)]
     L.wfa_stream_probe.argtypes = [vp, vp, sz, i32, ctypes.POINTER(dbl), vp]
@@ -334,6 +336,12 @@ class Grid:
         _check(lib().wfa_kernel_stats(self._h, int(kernel), ctypes.byref(n), ctypes.byref(ms),
                                       ctypes.byref(by), int(reset)))
         return n.value, ms.value, by.value
+
+    def resident_stats(self, reset: bool = False):
+        """(launches of resident iterations, those of them that gave up)."""
+        n, up = ctypes.c_int64(), ctypes.c_int64()
+        _check(lib().wfa_resident_stats(self._h, ctypes.byref(n), ctypes.byref(up), int(reset)))
+        return n.value, up.value
 
     def tiling(self):
         v = [ctypes.c_int() for _ in range(4)]
