@@ -243,12 +243,13 @@ enum {
                                   the *_solve entry points name their method) */
   WFA_OPT_PERSISTENT = 2,      /* 0 (default): one launch per phase, or, on
                                   grids small enough to keep their vectors in
-                                  registers, one cooperative launch per chunk
-                                  of iterations (bitwise the same results; not
+                                  registers, one launch per chunk of
+                                  iterations (bitwise the same results; not
                                   with WFA_OPT_PROFILE, _GRAPH or
-                                  _RECOMPUTE_T).  Such a launch needs all its
-                                  workgroups on the GPU at once.  Where other
-                                  streams' or processes' kernels keep one off
+                                  _RECOMPUTE_T, and not while such solves of
+                                  other threads fill the GPU).  A launch of
+                                  that form needs all its workgroups on the GPU
+                                  at once.  Where other kernels keep one off
                                   for some 0.1 s it gives up; that solve and
                                   the grid's next 255 then go on with one
                                   launch per pass (wfa_resident_stats);

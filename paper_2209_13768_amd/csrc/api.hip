@@ -773,16 +773,22 @@ static void graph_key(uint64_t (&k)[GraphCache::kKey], const wfa_grid* g, const 
 // resident iterations
 // ---------------------------------------------------------------------------
 // Grids whose tiles all fit on the chip with their vectors in registers
-// iterate in one cooperative launch per chunk (resident.hip): bitwise the
-// iterates of one launch per pass.  Not where the caller asked for another
-// launch form or for per-launch timing, and not without a pinned block (the
-// allocation-free solve: a first cooperative launch makes the runtime create
-// a queue).
+// iterate in one launch per chunk (resident.hip): bitwise the iterates of one
+// launch per pass.  Not where the caller asked for another launch form or for
+// per-launch timing, and not in the allocation-free solve, which makes the
+// launches it always made.
 template <typename T>
 static bool use_resident(const wfa_grid* g, const Launch<T>& L, int kind) {
   if (g->per_pass_solves > 0) return false;
   if (g->profile || g->persistent != 0 || g->recompute_t || g->rb.sync || use_graph(g)) return false;
   return resident_fits<T>(L, kind);
+}
+
+// Gives up the resident form (L.ring) where the solve would iterate so and
+// gets no turn.
+template <typename T>
+static void take_turn(const wfa_grid* g, Launch<T>& L, int kind, ResidentTurn& turn) {
+  if (use_resident(g, L, kind) && !turn.take(L.tl.geo.ntiles)) L.ring = nullptr;
 }
 
 // Iterations of one resident launch: the solve leaves it when it ends, so
@@ -793,8 +799,7 @@ static int resident_chunk(const wfa_grid* g, int budget) {
 }
 
 // A resident launch gave up: its workgroups were not all on a CU within the
-// bound of their waits (0.07 s each), because another stream's or process's
-// kernels held some.  What the iterations had in the workspace is lost; x is
+// bound of their waits (0.07 s each), because other kernels held some.  What the iterations had in the workspace is lost; x is
 // as it was when the launch started, or holds a newer iterate in some tiles.
 // The solve goes on from x with one launch per pass, and so do the grid's next
 // solves: whoever holds the CUs may do so for longer, and giving up costs as
@@ -1170,6 +1175,11 @@ static int solve_plain(wfa_grid* g, const T* b_user, T* x, bool form_b, double t
   Scalars h = fresh_scalars(tol, maxit, g->force_bd);
   g->force_bd = 0;
   Launch<T> L = ctx<T>(g, g->sc, s);
+  ResidentTurn turn;
+  take_turn(g, L, g->method == WFA_METHOD_CG ? kResidentCg
+                  : g->method == WFA_METHOD_CG1 ? kResidentCg1
+                  : g->method == WFA_METHOD_BICGSTAB2 ? kResidentBicgstab2 : kResidentBicgstab,
+            turn);
   Scalars ha = fresh_scalars(1.0, 1, 0);
   const bool use_tail = !g->profile;
   int rc = write_solve_scalars(L, &h, use_tail ? &ha : nullptr, g->sc_aux);
@@ -1281,6 +1291,8 @@ static int solve_ir(wfa_grid* g, const double* b_user, double* x, bool form_b, d
   float* w[2] = {v[0], v[1]};
   Launch<float> L32 = ctx<float>(g, g->sc_in, s);
   L32.op.jac = cg1 ? 0 : 1;
+  ResidentTurn turn;
+  take_turn(g, L32, cg1 ? kResidentCg1 : kResidentBicgstab2, turn);
   // the inner solve's shadow residual (as the residual pass writes it); a
   // refinement whose inner solve diverged without a usable iterate under the
   // hashed one is repeated with r^ = r0, kept for the rest of the solve

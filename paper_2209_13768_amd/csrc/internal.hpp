@@ -129,7 +129,7 @@ hipError_t launch_persistent_bicgstab(const Launch<T>& L, T* x, T* r, const T* r
                                       T* v0, T* v1, T* t, int iters, int parity,
                                       GridBarrier* bar);
 
-// Resident iterations of small grids (one cooperative launch per chunk, the
+// Resident iterations of small grids (one launch per chunk, the
 // vectors in registers; the iterates bitwise those of the per-pass
 // launches).  r, p, v: the double-buffered pairs, those of `parity` in.
 enum ResidentKind {
@@ -144,6 +144,23 @@ struct ResidentVectors {
   const T* rh;
   T* t;
   T *r[2], *p[2], *v[2];
+};
+// A solve's turn to iterate resident: its launches and those of the other
+// solves of the process, on whichever streams, must all find room, or each
+// could wait for workgroups that another keeps out.  A workgroup is counted as
+// a CU, however small: wherever those of one launch have gone, as many CUs as
+// it has none of are free of it.  A solve that gets none takes one launch per
+// pass.
+class ResidentTurn {
+ public:
+  ResidentTurn() = default;
+  ResidentTurn(const ResidentTurn&) = delete;
+  ResidentTurn& operator=(const ResidentTurn&) = delete;
+  ~ResidentTurn();
+  bool take(int tiles);   // on the current device, until the object goes
+
+ private:
+  int dev_ = 0, tiles_ = 0;
 };
 int ring_copies(size_t doubles, int ntiles);
 template <typename T>

@@ -1,4 +1,4 @@
-// Resident Krylov iterations of small grids: one cooperative launch runs a
+// Resident Krylov iterations of small grids: one launch runs a
 // whole chunk of iterations of one solve with its vectors held in registers.
 //
 // A small grid's iteration is latency, not traffic: at 32^3 each pass was a
@@ -33,6 +33,14 @@
 // per launch (in LDS, or for a constant diffusivity in registers); the
 // finalizer runs on registers.
 //
+// The launch is an ordinary one.  Cooperative launches of a process pass
+// through one queue, so that solves of several threads took turns, and waited
+// for the streams' queues at each change.  Small heat steps a second from 1, 4
+// and 16 threads, one launch per pass / resident, cooperative / ordinary with
+// turns: 16^3 CG with one reduction 3046, 6309, 10027 / 7451, 10640, 8840 /
+// 8670, 19050, 19090; 32^3 BiCGStab 1249, 4237, 4461 / 3560, 4380, 4060 / 3850,
+// 11320, 5450; 64^3 refined 509, 1494, 1349 / 1310, 1630, 1340 / 1460, 2470, 1880.
+//
 // Measured (us an iteration, one launch per pass -> resident; FP64 constant
 // diffusivity, then FP32 per cell):
 //   textbook BiCGStab       32^3 24.8 -> 6.6   64^3 32.7 -> 10.9
@@ -51,9 +59,9 @@
 // finalizers are those of the per-pass kernels, so the iterates are bitwise
 // theirs.
 //
-// A wait needs every workgroup of the launch on a CU, which other streams' or
-// processes' kernels may prevent for as long as they like; waits are therefore
-// bounded.  A workgroup that gives up sets the scalar block's `timeout` and
+// A wait needs every workgroup of the launch on a CU.  The launches of one
+// process see to that among themselves (ResidentTurn), but other kernels may
+// prevent it for as long as they like; waits are therefore bounded.  A workgroup that gives up sets the scalar block's `timeout` and
 // leaves, and so does every other at its next wait, each with x as it has it;
 // the solve goes on from that x with one launch per pass.  Once the launch's
 // first exchange has passed, every workgroup holds its CU and later waits end.
@@ -929,6 +937,21 @@ __global__ void __launch_bounds__(kThreads) k_resident_cg1(ResArgs<T> a) {
 }
 #undef WFA_RESIDENT_BEGIN
 
+// The current device and its CUs (looked up once), or false.
+constexpr int kDevices = 16;
+bool this_device(int& dev, int& cus) {
+  static std::atomic<int> known[kDevices];
+  dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return false;
+  cus = known[dev].load(std::memory_order_relaxed);
+  if (cus > 0) return true;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus < 1)
+    return false;
+  known[dev].store(cus, std::memory_order_relaxed);
+  return true;
+}
+
 // A kernel and the workgroups of it that fit on the current device at once
 // (looked up once per device).
 template <typename T>
@@ -939,16 +962,14 @@ struct Entry {
 
 template <typename T, void (*K)(ResArgs<T>)>
 Entry<T> entry() {
-  constexpr int kDevices = 16;
   static std::atomic<int> known[kDevices];
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return {};
+  int dev, cus;
+  if (!this_device(dev, cus)) return {};
   int fit = known[dev].load(std::memory_order_relaxed);
   if (fit == 0) {
-    int per_cu = 0, cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)K, kThreads, 0) !=
-            hipSuccess)
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)K, kThreads, 0) !=
+        hipSuccess)
       return {};
     fit = per_cu * cus;
     known[dev].store(fit, std::memory_order_relaxed);
@@ -978,6 +999,26 @@ Entry<T> entry_for(const Launch<T>& L, int kind) {
 }
 
 }  // namespace
+
+// Tiles of the solves that have a turn, by device.
+static std::atomic<int> g_tiles[kDevices];
+
+bool ResidentTurn::take(int tiles) {
+  int dev, cus;
+  if (!this_device(dev, cus)) return false;
+  const int others = g_tiles[dev].fetch_add(tiles, std::memory_order_relaxed);
+  if (others > 0 && others + tiles > cus) {
+    g_tiles[dev].fetch_sub(tiles, std::memory_order_relaxed);
+    return false;
+  }
+  dev_ = dev;
+  tiles_ = tiles;
+  return true;
+}
+
+ResidentTurn::~ResidentTurn() {
+  if (tiles_) g_tiles[dev_].fetch_sub(tiles_, std::memory_order_relaxed);
+}
 
 template <typename T>
 bool resident_fits(const Launch<T>& L, int kind) {
@@ -1012,8 +1053,8 @@ hipError_t launch_resident(const Launch<T>& L, int kind, const ResidentVectors<T
   a.parity = parity;
   a.hashed = L.shadow;
   void* args[] = {(void*)&a};
-  return hipLaunchCooperativeKernel((const void*)entry_for<T>(L, kind).kernel, dim3(a.geo.ntiles - (absent ? 1 : 0)),
-                                    dim3(kThreads), args, 0, L.stream);
+  return hipLaunchKernel((const void*)entry_for<T>(L, kind).kernel,
+                         dim3(a.geo.ntiles - (absent ? 1 : 0)), dim3(kThreads), args, 0, L.stream);
 }
 
 // The solve's scalars, with every slot of the ring empty.

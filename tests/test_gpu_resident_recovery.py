@@ -158,3 +158,35 @@ def test_two_streams_whose_grids_do_not_fit_side_by_side(wfa):
         t.join()
     for q in range(2):
         assert all(torch.equal(x, alone[q]) for x in got[q])
+
+
+def test_more_solves_at_once_than_fit_the_gpu(wfa):
+    """Eight threads whose grids have 40 to 160 workgroups: solves that get no
+    turn take one launch per pass, none waits in vain, and each gives what it
+    gives alone."""
+    import threading
+    import torch
+    shapes = [(64, 64, 160), (70, 45, 38), (40, 33, 21), (97, 61, 45)]
+    probs = [_problem(shapes[q % 4], "cg1", 720 + q, cell=q % 2 == 0) for q in range(8)]
+
+    def solve(prob, n):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            g = wfa.Grid.from_problem(prob, precision="f64")
+            b = g.rhs(g.field(prob.T0))
+            xs = [g.solve(b, g.field(prob.T0), tol=1e-11, maxit=2000, method="cg1")[0].cpu()
+                  for _ in range(n)]
+            return xs, g.resident_stats()
+    alone = [solve(p, 1)[0][0] for p in probs]
+    got = [None] * 8
+
+    def work(q):
+        got[q] = solve(probs[q], 6)
+    ts = [threading.Thread(target=work, args=(q,)) for q in range(8)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for q in range(8):
+        xs, (launches, gave_up) = got[q]
+        assert all(torch.equal(x, alone[q]) for x in xs) and gave_up == 0, q
+    assert sum(s[0] for _, s in got) > 0
