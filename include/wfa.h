@@ -254,7 +254,8 @@ enum {
                                   the grid's next 255 then go on with one
                                   launch per pass (wfa_resident_stats);
                                   1: one persistent launch per solve chunk,
-                                  -1: automatic by grid size                   */
+                                  -1: as 0 where the grid iterates resident,
+                                  else as 1 up to 2^21 cells                   */
   WFA_OPT_PROFILE = 3,         /* n > 0: time every n-th launch of each
                                   kernel with HIP events (1: every launch;
                                   the count restarts when the option is
@@ -286,7 +287,8 @@ enum {
                                   host checks from captured HIP graphs of 8
                                   iterations (results are bitwise those of
                                   plain launches); 0: plain launches (default);
-                                  -1: graphs for grids up to 2^23 cells        */,
+                                  -1: graphs for grids up to 2^23 cells that
+                                  do not iterate resident                      */,
   WFA_OPT_EXPLICIT_FUSE = 11   /* explicit steps per pass over memory in
                                   wfa_explicit_step: 1 to 4; 0 = automatic
                                   (with a constant diffusivity by grid size,
@@ -329,7 +331,7 @@ enum {
                                   up to 96^3, 152^3 and above)                */
   WFA_OPT_FORCE_GIVE_UP = 19   /* n > 0: one workgroup is missing from the
                                   grid's n-th launch of resident iterations
-                                  from now (WFA_OPT_PERSISTENT 0), as if
+                                  from now (WFA_OPT_PERSISTENT), as if
                                   another kernel held its CU, so that the
                                   launch gives up (once), to exercise the
                                   recovery from the host                      */
@@ -349,7 +351,7 @@ enum {
 int wfa_kernel_stats(wfa_grid* g, int kernel, int64_t* launches, double* ms,
                      double* bytes_per_launch, int reset);
 
-/* Launches of resident iterations (WFA_OPT_PERSISTENT 0) the grid's solves
+/* Launches of resident iterations (WFA_OPT_PERSISTENT) the grid's solves
  * have made since it was created or since the last reset, and how many of
  * them gave up.  Either pointer may be NULL; reset != 0 clears both. */
 int wfa_resident_stats(wfa_grid* g, int64_t* launches, int64_t* gave_up, int reset);

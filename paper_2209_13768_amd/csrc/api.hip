@@ -656,16 +656,17 @@ static int next_chunk(const wfa_grid* g, const Scalars& h, int budget, int hint)
 // ---------------------------------------------------------------------------
 // persistent launches
 // ---------------------------------------------------------------------------
-// Grids up to this many cells iterate in one cooperative launch per chunk by
-// default: below it, launch and dependency latency outweighs the three
-// kernel boundaries' cache effects.
+// Automatic choice (-1): grids up to this many cells that don't iterate
+// resident do so in one cooperative launch per chunk.  Below it, launch and
+// dependency latency outweighs the three kernel boundaries' cache effects.
 static const size_t kPersistentCells = (size_t)1 << 21;
 
-static bool use_persistent(const wfa_grid* g, const Tiling& tl) {
-  (void)tl;
+template <typename T>
+static bool use_persistent(const wfa_grid* g, const Launch<T>& L, bool resident) {
   if (g->persistent == 1) return true;
-  if (g->persistent == 0) return false;
-  return g->n <= kPersistentCells;
+  // (without a ring the GPU is full of resident launches, or a launch found no
+  // room on it: not the time for another that needs all its workgroups there)
+  return g->persistent == -1 && !resident && L.ring && g->n <= kPersistentCells;
 }
 
 static GridBarrier* barrier_of(wfa_grid* g) { return (GridBarrier*)(g->sc + 3); }
@@ -774,13 +775,15 @@ static void graph_key(uint64_t (&k)[GraphCache::kKey], const wfa_grid* g, const 
 // ---------------------------------------------------------------------------
 // Grids whose tiles all fit on the chip with their vectors in registers
 // iterate in one launch per chunk (resident.hip): bitwise the iterates of one
-// launch per pass.  Not where the caller asked for another launch form or for
+// launch per pass, in a third to two thirds of their time and less than the
+// persistent launch's or a graph's, whose automatic choices therefore leave
+// these grids to it.  Not where the caller asked for another launch form or for
 // per-launch timing, and not in the allocation-free solve, which makes the
 // launches it always made.
 template <typename T>
 static bool use_resident(const wfa_grid* g, const Launch<T>& L, int kind) {
   if (g->per_pass_solves > 0) return false;
-  if (g->profile || g->persistent != 0 || g->recompute_t || g->rb.sync || use_graph(g)) return false;
+  if (g->profile || g->persistent == 1 || g->recompute_t || g->rb.sync || g->graph == 1) return false;
   return resident_fits<T>(L, kind);
 }
 
@@ -875,7 +878,8 @@ static int iterate_bicgstab(wfa_grid* g, const Launch<T>& L, T* x, T* r, T* spar
   int par = 0;
   int rc = WFA_OK;
   bool resident = use_resident(g, L, kResidentBicgstab);
-  if (use_persistent(g, L.tl)) {
+  const bool persistent = use_persistent(g, L, resident);
+  if (persistent) {
     if ((rc = reset_barrier(g, L.stream))) return rc;
     if ((rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
   }
@@ -889,7 +893,7 @@ static int iterate_bicgstab(wfa_grid* g, const Launch<T>& L, T* x, T* r, T* spar
       }
       if ((rc = check_launch("init"))) return rc;
       h->restart = 0;
-      if (use_persistent(g, L.tl) && (rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
+      if (persistent && (rc = read_chunk(g, L.sc, h, L.stream, tail))) return rc;
       continue;
     }
     if (resident) {
@@ -904,7 +908,7 @@ static int iterate_bicgstab(wfa_grid* g, const Launch<T>& L, T* x, T* r, T* spar
       continue;
     }
     const int m = next_chunk(g, *h, h->maxit - h->iter, hint);
-    if (use_persistent(g, L.tl)) {
+    if (persistent) {
       hipError_t e;
       {
         ProfScope ps(g, WFA_K_PERSISTENT, L.stream);

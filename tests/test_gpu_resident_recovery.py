@@ -95,6 +95,22 @@ def test_solve_goes_on_per_pass_when_a_launch_gives_up(wfa, precision, method, s
     assert g.resident_stats() == (0, 0) and _same(x, xr)
 
 
+@pytest.mark.parametrize("option", ["OPT_PERSISTENT", "OPT_GRAPH"])
+@pytest.mark.parametrize("method", METHODS)
+def test_automatic_launch_forms_leave_small_grids_resident(wfa, method, option):
+    for shape, resident in (((41, 30, 22), True), ((97, 88, 99), False)):
+        prob = _problem(shape, method, 44)
+        out = []
+        for value in (0, -1):
+            g = wfa.Grid.from_problem(prob, precision="f64")
+            g.set_option(getattr(wfa, option), value)
+            b = g.rhs(g.field(prob.T0))
+            x, i = g.solve(b, g.field(prob.T0), tol=1e-300, maxit=20, method=method, check=False)
+            assert (g.resident_stats()[0] > 0) == resident, (shape, value)
+            out.append((x, i.iterations))
+        assert out[0][1] == out[1][1] and _same(out[0][0], out[1][0]), shape
+
+
 @pytest.mark.parametrize("method", METHODS)
 def test_later_chunks_count_on_from_the_iterations_made(wfa, oracle_mod, method):
     """Chunks of four iterations, the workgroup missing from the second: the
