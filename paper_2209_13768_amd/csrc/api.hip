@@ -110,8 +110,10 @@ static Op<T> make_op(const wfa_coeffs& c) {
     const double F = c.dt * (c.u[axis] * normal) / c.h;
     op.in[f] = (T)fmax(-F, 0.0);
     op.out[f] = (T)fmax(F, 0.0);
-    op.bval[f] = (T)c.bc_value[f];
-    if (c.bc[f] == WFA_BC_DIRICHLET) op.dir |= 1u << f;
+    if (c.bc[f] == WFA_BC_DIRICHLET) {
+      op.bval[f] = (T)c.bc_value[f];
+      op.dir |= 1u << f;
+    }
     if (op.in[f] != T(0) || op.out[f] != T(0)) op.conv = 1;
   }
   return op;
@@ -1566,6 +1568,12 @@ extern "C" int wfa_explicit_step(wfa_grid* g, void* T, int nsteps, void* stream)
     else if (g->prec != WFA_F32) fuse = 3;
     else fuse = g->n < ((size_t)40 << 20) ? 2 : g->n < ((size_t)100 << 20) ? 3 : 4;
   }
+  // A fused pass multiplies every cell on a face by the ghost values of all
+  // faces, with coefficient 0 where it has none; a value past FP32's range
+  // takes the single step, which branches.
+  if (g->prec == WFA_F32)
+    for (float v : g->op32.bval)
+      if (!isfinite(v)) fuse = 1;
   // The passes alternate between T and the second time level: an even number
   // of them, where the steps can be shared out so, ends in T without a copy.
   // (Not where the caller set the steps per pass: there the last pass takes

@@ -76,7 +76,7 @@ struct Op {
   T cD;            // dt/h^2 (CELL) or dt*alpha/h^2 (CONST)
   T in[6];         // inflow coupling per face:  max(-F_f, 0)
   T out[6];        // outflow diagonal per face: max( F_f, 0)
-  T bval[6];       // Dirichlet ghost values
+  T bval[6];       // Dirichlet ghost values (0 on other faces)
   uint32_t dir;    // bit f set: face f is Dirichlet
   uint32_t jac;    // 1: the Krylov operator is D^{-1} A (left Jacobi scaling)
   uint32_t conv;   // 1: some face has a convective term (in[f] or out[f] != 0)

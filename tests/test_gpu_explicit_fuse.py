@@ -62,3 +62,32 @@ def test_every_depth_at_the_range_of_buffer_offsets(wfa, precision, rows, over, 
     T, fused, single = _run(wfa, shape, precision, 2 * fuse, fuse, T0)
     assert (fused, single) == (2, 0)
     assert torch.equal(T, _run(wfa, shape, precision, 2 * fuse, 1, T0)[0])
+
+
+@pytest.mark.parametrize("fuse", [2, 3, 4])
+@pytest.mark.parametrize("kind", ["zero-flux", "dirichlet"])
+def test_a_ghost_value_past_fp32_stays_at_its_face(wfa, kind, fuse):
+    """1e300 is infinite in FP32: ignored on a zero-flux face, and on a
+    Dirichlet face what the cells next to it see, not the rest of their rows
+    and planes."""
+    import torch
+    shape = (70, 45, 38)
+    h = inputs.grid_spacing(*shape)
+    T0 = _field(shape, "f32")
+    for face in range(6):
+        out = []
+        for n in (1, fuse):
+            bc = [wfa.BC_DIRICHLET] * 6
+            if kind == "zero-flux":
+                bc[face] = wfa.BC_ZEROFLUX
+            g = wfa.Grid(*shape, h=h, dt=0.1 * h * h, bc=bc, precision="f32",
+                         bc_value=[1e300 if f == face else 0.5 for f in range(6)])
+            g.set_option(wfa.OPT_EXPLICIT_FUSE, n)
+            out.append(g.explicit(T0.clone(), 2 * fuse))
+        a, b = out
+        finite = torch.isfinite(a)
+        assert torch.equal(finite, torch.isfinite(b)), face
+        assert torch.equal(a[finite], b[finite]), face
+        # a step carries the face's infinity one cell further
+        assert int((~finite).sum()) == (0 if kind == "zero-flux" else
+                                        2 * fuse * (T0.numel() // shape[face // 2])), face
