@@ -135,6 +135,7 @@ template <typename T>
 int batch_build(const SolveDesc<T>* d, int nsolves, int ry) {
   if (ry != 2 || nsolves < 1) return kBatchAny;
   const int form = op_form(d[0].op), cell = d[0].cell;
+  if (sizeof(T) == 8 && form_scaled(form)) return kBatchAny;
   for (int s = 0; s < nsolves; ++s)
     if (d[s].cg1 || !d[s].hashed || d[s].cell != cell || op_form(d[s].op) != form)
       return kBatchAny;
@@ -172,8 +173,12 @@ void launch_batch_iteration2(const SolveDesc<T>* descs, const int* tile_bases, i
   switch (build) {
     WFA_BATCH(kFormDiffusion);
     WFA_BATCH(kFormConvection);
-    WFA_BATCH(kFormDiffusionScaled);
-    WFA_BATCH(kFormConvectionScaled);
+  }
+  if constexpr (sizeof(T) == 4) {   // only refined requests' inner solves are scaled
+    switch (build) {
+      WFA_BATCH(kFormDiffusionScaled);
+      WFA_BATCH(kFormConvectionScaled);
+    }
   }
 #undef WFA_BATCH
   switch (ry) {

@@ -299,41 +299,6 @@ __device__ __forceinline__ T cell_bterm(const Op<T>& op, T kP, uint32_t inside) 
   return s;
 }
 
-// Coefficients of a constant-diffusivity operator at a cell whose six
-// neighbours all exist, formed in the order cell_apply forms them, so that
-// cell_apply_interior returns cell_apply's value bit for bit.
-template <typename T>
-struct InteriorCoef {
-  T coef[6];  // D + in[f]
-  T diag;     // 1 + sum_f (D + out[f]), summed in face order
-};
-
-template <typename T>
-__device__ __forceinline__ InteriorCoef<T> interior_coef(const Op<T>& op) {
-#pragma clang fp contract(off)
-  InteriorCoef<T> k;
-  T diag = T(1);
-#pragma unroll
-  for (int f = 0; f < 6; ++f) {
-    diag += op.cD + op.out[f];
-    k.coef[f] = op.cD + op.in[f];
-  }
-  k.diag = diag;
-  return k;
-}
-
-// (A x)_P of a constant-diffusivity operator at a cell with all six
-// neighbours inside and no Jacobi scaling: cell_apply's operation sequence
-// with the face tests resolved.
-template <typename T>
-__device__ __forceinline__ T cell_apply_interior(const InteriorCoef<T>& k, T c, const T nb[6]) {
-#pragma clang fp contract(off)
-  T acc = T(0);
-#pragma unroll
-  for (int f = 0; f < 6; ++f) acc = fma_t(k.coef[f], nb[f], acc);
-  return fma_t(k.diag, c, -acc);
-}
-
 // Shadow residual computed from the cell index instead of stored: the
 // 32-bit PCG hash of the index (an LCG step, state = i * 747796405 +
 // 2891336453, then PCG's RXS-M-XS output permutation; O'Neill 2014), whose
