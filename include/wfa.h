@@ -272,7 +272,10 @@ enum {
                                   previous converged solve (else 8), later
                                   ones an estimate from the residual history.
                                   Passes queued past convergence exit at
-                                  once, so results never depend on this.      */
+                                  once, so results never depend on this.
+                                  Resident iterations (WFA_OPT_PERSISTENT)
+                                  leave their launch when the solve ends and
+                                  take 512 a launch where this is 0           */
   WFA_OPT_IR_INNER_TOL = 6,    /* (value / 1e12) = inner relative tolerance of
                                   WFA_F32_IR64; default 1e-4 * 1e12            */
   WFA_OPT_ZCHUNK = 7,          /* z planes per workgroup; 0 = default rule     */

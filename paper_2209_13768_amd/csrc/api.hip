@@ -641,7 +641,8 @@ static int next_chunk(const wfa_grid* g, const Scalars& h, int budget, int hint)
   } else if (h.iter == 0 && hint > 0) {
     m = hint;
   } else if (h.iter == 0 || !(h.rr > 0.0) || !(h.rr0 > 0.0) || h.rr >= h.rr0) {
-    // no estimate: more as the solve goes on, a quarter of it at most wasted
+    // no estimate: more as the solve goes on; at most 8 iterations and a quarter
+    // of those made are wasted
     m = h.iter < 480 ? 8 + h.iter / 4 : 128;
   } else {
     const double rate = log(h.rr / h.rr0) / (double)h.iter;  // < 0
