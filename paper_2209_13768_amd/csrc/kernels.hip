@@ -407,11 +407,14 @@ Tiling make_tiling(int nx, int ny, int nz, int elem_bytes, int zc_override, int 
   // hints and whole rows (textbook BiCGStab per iteration: 256^3 FP64 497 ->
   // 441 us, 512^3 FP32 2350 -> 2264 us); between them a tile per workgroup
   // is too few (161x97x113, 312 tiles: 107 -> 116 us), and rows that do not
-  // fill the tiles' lanes give the gain back (174x158x392: 5% slower).  zc >=
-  // 2: so many tiles' sums fit a persistent launch's regions.
+  // fill the tiles' lanes give the gain back (174x158x392: 5% slower).  So do
+  // tiles of few planes, whose workgroups come and go for little: 256^3 classic
+  // CG FP32, tiles of 4, 6, 8 and 16 planes 194, 169, 159, 153 -> 232, 183, 152,
+  // 140 us; FP64 2, 3 and 4 planes 394, 332, 307 -> 447, 333, 266.  (So many
+  // tiles' sums also fit a persistent launch's regions.)
   t.tile_order = t.ry == kTileOrderRows &&
                  ((g.ntiles <= kResidentTiles && g.zc <= resident_planes(elem_bytes)) ||
-                  (g.ntiles >= 1024 && g.zc >= 2 && nx % kTX == 0));
+                  (g.ntiles >= 1024 && g.zc * elem_bytes >= 32 && nx % kTX == 0));
   return t;
 }
 
