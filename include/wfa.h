@@ -293,8 +293,8 @@ enum {
                                   -1: graphs for grids up to 2^23 cells that
                                   do not iterate resident                      */,
   WFA_OPT_EXPLICIT_FUSE = 11   /* explicit steps per pass over memory in
-                                  wfa_explicit_step: 1 to 4 (the last pass of
-                                  a call takes the steps left over); 0 = automatic
+                                  wfa_explicit_step: 1 to 4 (the steps left
+                                  over go one by one); 0 = automatic
                                   (with a constant diffusivity by grid size,
                                   up to 4 in FP32 and 3 in FP64, else 1).  More
                                   than 1 needs WFA_COEF_CONST                  */,

@@ -1577,14 +1577,13 @@ extern "C" int wfa_explicit_step(wfa_grid* g, void* T, int nsteps, void* stream)
       if (!isfinite(v)) fuse = 1;
   // The passes alternate between T and the second time level: an even number
   // of them, where the steps can be shared out so, ends in T without a copy.
-  // (Not where the caller set the steps per pass: there the last pass takes
-  // the steps left over.)
-  int passes = nsteps / fuse + (nsteps % fuse ? 1 : 0);
-  if (g->fuse == 0 && (passes & 1) && passes < nsteps && fuse > 1) ++passes;
-  for (int pass = 0, done = 0; pass < passes; ++pass) {
-    int k = nsteps / passes + (pass < nsteps % passes ? 1 : 0);
-    if (g->fuse > 0) k = fuse < nsteps - done ? fuse : nsteps - done;
-    done += k;
+  // Where the caller set the steps per pass, the steps left over go one by one.
+  const bool set = g->fuse > 0;
+  int passes = nsteps / fuse + (set ? nsteps % fuse : nsteps % fuse ? 1 : 0);
+  if (!set && (passes & 1) && passes < nsteps && fuse > 1) ++passes;
+  for (int pass = 0; pass < passes; ++pass) {
+    const int k = set ? (pass < nsteps / fuse ? fuse : 1)
+                      : nsteps / passes + (pass < nsteps % passes ? 1 : 0);
     const void* in = bufs[pass & 1];
     void* out = bufs[(pass + 1) & 1];
     if (k > 1) {

@@ -44,8 +44,7 @@ def test_steps_per_pass_are_those_set(wfa, precision, fuse):
     T0 = _field(shape, precision)
     for nsteps in (0, 1, 2, 3, 4, 6, 7, 9, 12):
         T, fused, single = _run(wfa, shape, precision, nsteps, fuse, T0)
-        rest = nsteps % fuse
-        expect = (nsteps // fuse + (rest > 1), int(rest == 1)) if fuse > 1 else (0, nsteps)
+        expect = (nsteps // fuse, nsteps % fuse) if fuse > 1 else (0, nsteps)
         assert (fused, single) == expect, (nsteps, fused, single)
         assert torch.equal(T, _run(wfa, shape, precision, nsteps, 1, T0)[0]), nsteps
 
