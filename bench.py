@@ -55,10 +55,11 @@ HEADLINE_ITERS = 500
 HEADLINE_TIME_EVERY = 8   # the timed steps time one launch in 8 of each kernel
 
 
-# The files that define the single-grid solver kernels and their launch
-# shapes: counter figures taken from other sources are stale.
-# sources of the stencil passes, and of the copy that calibrates the counters
-KERNEL_SOURCES = ("device.hpp", "phases.hpp", "kernels.hip", "probes.hip")
+# The files that define the single-grid kernels and their launch shapes, and
+# the copy that calibrates the counters: counter figures taken from other
+# sources are stale.
+KERNEL_SOURCES = ("device.hpp", "phases.hpp", "kernels.hip", "explicit_tb.hip", "fused_ac.hip",
+                  "resident.hip", "probes.hip")
 
 
 def kernel_source_hash() -> str:

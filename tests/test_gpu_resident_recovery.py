@@ -206,3 +206,35 @@ def test_more_solves_at_once_than_fit_the_gpu(wfa):
         xs, (launches, gave_up) = got[q]
         assert all(torch.equal(x, alone[q]) for x in xs) and gave_up == 0, q
     assert sum(s[0] for _, s in got) > 0
+
+
+def test_resident_solves_beside_persistent_launches_and_large_passes(wfa):
+    """Other kernels that need or hold many CUs, from threads of their own: a
+    persistent launch of as many workgroups, and the passes of a grid that
+    fills the GPU.  Every solve gives what it gives alone."""
+    import threading
+    import torch
+    small = _problem((64, 64, 160), "bicgstab", 731)
+    large = _problem((200, 180, 160), "bicgstab2", 732)
+
+    def solve(prob, method, persistent, n, maxit):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            g = wfa.Grid.from_problem(prob, precision="f64")
+            g.set_option(wfa.OPT_PERSISTENT, persistent)
+            b = g.rhs(g.field(prob.T0))
+            return [g.solve(b, g.field(prob.T0), tol=1e-300, maxit=maxit, method=method)[0].cpu()
+                    for _ in range(n)]
+    works = [(small, "bicgstab", 0, 12, 60), (small, "bicgstab", 1, 6, 60),
+             (small, "bicgstab", 0, 12, 60), (large, "bicgstab2", 0, 4, 40)]
+    alone = [solve(p, m, per, 1, k)[0] for p, m, per, _, k in works]
+    got = [None] * len(works)
+
+    def work(q):
+        got[q] = solve(*works[q])
+    ts = [threading.Thread(target=work, args=(q,)) for q in range(len(works))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for q in range(len(works)):
+        assert got[q] is not None and all(_same(x, alone[q]) for x in got[q]), q
