@@ -61,10 +61,11 @@
 //
 // A wait needs every workgroup of the launch on a CU.  The launches of one
 // process see to that among themselves (ResidentTurn), but other kernels may
-// prevent it for as long as they like; waits are therefore bounded.  A workgroup that gives up sets the scalar block's `timeout` and
-// leaves, and so does every other at its next wait, each with x as it has it;
-// the solve goes on from that x with one launch per pass.  Once the launch's
-// first exchange has passed, every workgroup holds its CU and later waits end.
+// prevent it for as long as they like; waits are therefore bounded.  A
+// workgroup that gives up sets the scalar block's `timeout` and leaves, and so
+// does every other at its next wait, each with x as it has it; the solve goes
+// on from that x with one launch per pass.  Once the launch's first exchange
+// has passed, every workgroup holds its CU and later waits end.
 #include <stddef.h>
 
 #include <atomic>
