@@ -778,7 +778,7 @@ static void graph_key(uint64_t (&k)[GraphCache::kKey], const wfa_grid* g, const 
 // ---------------------------------------------------------------------------
 // Grids whose tiles all fit on the chip with their vectors in registers
 // iterate in one launch per chunk (resident.hip): bitwise the iterates of one
-// launch per pass, in a third to two thirds of their time and less than the
+// launch per pass, in a quarter to two thirds of their time and less than the
 // persistent launch's or a graph's, whose automatic choices therefore leave
 // these grids to it.  Not where the caller asked for another launch form or for
 // per-launch timing, and not in the allocation-free solve, which makes the
@@ -805,11 +805,12 @@ static int resident_chunk(const wfa_grid* g, int budget) {
 }
 
 // A resident launch gave up: its workgroups were not all on a CU within the
-// bound of their waits (0.07 s each), because other kernels held some.  What the iterations had in the workspace is lost; x is
-// as it was when the launch started, or holds a newer iterate in some tiles.
-// The solve goes on from x with one launch per pass, and so do the grid's next
-// solves: whoever holds the CUs may do so for longer, and giving up costs as
-// much as some hundred small solves.
+// bound of their waits (0.07 s each), because other kernels held some.  What
+// the iterations had in the workspace is lost; x is as it was when the launch
+// started, or holds a newer iterate in some tiles.  The solve goes on from x
+// with one launch per pass, and so do the grid's next solves: whoever holds the
+// CUs may do so for longer, and giving up costs as much as some hundred small
+// solves.
 constexpr int kGaveUp = 1;
 constexpr int kPerPassSolves = 256;
 
